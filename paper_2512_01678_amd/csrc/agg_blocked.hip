@@ -1,0 +1,544 @@
+// agg_blocked.hip -- the aggregation with 16-byte rows wider than 16 columns.
+//
+// Z[u,:] = sum_{e in row u} val[e] * M[col[e], :]  (+ bias, epilogue), as in aggregate.hip, for
+// matrices M below 4 GB: a wavefront sums one row at a time over a panel of 4 LANES columns.
+//
+// What bounds it: every gather that misses the XCD's 4 MB L2 is served by the fabric behind it
+// at about 55-70 G random 128-byte lines/s (7-9 TB/s), and every 1 KB gather instruction takes
+// 16 cycles of the CU's address unit (measured busy 83 % of the time where the gathers hit).
+// So beside the gathers themselves the kernel issues little: entries are loaded contiguously
+// (one index and one value load per 64 entries, two chunks ahead), handed to the lanes by a
+// constant-pattern LDS swizzle, and rows are addressed by 32-bit offsets; a panel covers whole
+// lines, so that no line is fetched for two panels.
+//
+// Long rows: a piece of more than kHub entries is cut over the four wavefronts of its
+// workgroup; rows beyond GCN_SPLIT_MIN with a split plan are summed chunk by chunk by
+// wavefronts that start ahead of the others in the same launch.
+//
+// Dense graphs are blocked by source rows.  Gathered in row order, M is read from behind the L2
+// once per entry (4 nnz w bytes).  Where a row has enough entries in each block of M's rows
+// (agg_blocked_plan), one launch per block adds the block's share to every row, panel after
+// panel, so that a line is fetched into each L2 once and most further gathers of it hit there.
+// The entries of a row that fall into a block are a contiguous piece of it, found by binary
+// search at the start of the call.  Between the launches a row's partial sum rests in Z; the
+// last launch applies the epilogue.  Every sum has a fixed order: deterministic.
+//
+// Measured (us, before -> now, the same box): 232,965 rows of 484 entries, width 256 13,700 ->
+// 7,390, width 41 3,050 -> 1,930; 169,343 rows of 15, width 256 342 -> 306, 128 170 -> 157, 40
+// 106 -> 76; RMAT 2^21 rows of 31, width 128 4,000 -> 3,610; 2,449,029 rows of 51, width 256
+// 17,900 -> 17,600 (bound by the fabric); 100,000 rows of 32, width 128 272 -> 171.
+#include "agg_device.h"
+
+#include <cstdlib>
+
+namespace gcn {
+namespace {
+
+constexpr int kBlockThreads = 256;
+
+// A wavefront holds SL = 64 / LANES slices of LANES lanes and sums one row's piece at a time,
+// in chunks of up to 64 entries cut into SL runs; lane i of a slice requests the i-th entry of
+// its run, so that step u takes the entry of lane u of each slice: one LDS-crossbar swizzle
+// with a constant pattern, no index arithmetic per gather.
+template <int LANES, int U>
+__device__ __forceinline__ uint32_t from_lane(uint32_t v) {
+  constexpr int pattern = (U << 5) | (0x1f & ~(LANES - 1));  // and-mask keeps the slice, or-mask names lane U
+  return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, pattern);
+}
+
+// Gathers of steps U .. U + N - 1.  FULL: every slice has an entry in each; else step u is this
+// slice's only if u < mine (a skipped entry must not be multiplied by zero instead: the row
+// could hold an infinity).
+template <int LANES, int U, int N, bool FULL>
+__device__ __forceinline__ void gather_load(const char* Mc, uint32_t off, uint32_t lane_off, int mine, float4* x) {
+  auto load = [&](auto ic) __attribute__((always_inline)) {
+    constexpr int I = decltype(ic)::value;
+    const uint32_t o = from_lane<LANES, U + I>(off) + lane_off;
+    if constexpr (FULL) {
+      x[I] = *reinterpret_cast<const float4*>(Mc + o);
+    } else {
+      x[I] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (U + I < mine) x[I] = *reinterpret_cast<const float4*>(Mc + o);
+    }
+  };
+  [&]<int... I>(std::integer_sequence<int, I...>) { (load(std::integral_constant<int, I>{}), ...); }
+  (std::make_integer_sequence<int, N>{});
+}
+
+template <int LANES, int U, int N>
+__device__ __forceinline__ void gather_add(float w, const float4* x, float4& acc) {
+  auto add = [&](auto ic) __attribute__((always_inline)) {
+    constexpr int I = decltype(ic)::value;
+    Vec<4>::fma(acc, __uint_as_float(from_lane<LANES, U + I>(__float_as_uint(w))), x[I]);
+  };
+  [&]<int... I>(std::integer_sequence<int, I...>) { (add(std::integral_constant<int, I>{}), ...); }
+  (std::make_integer_sequence<int, N>{});
+}
+
+// Steps U .. U + 7 of a chunk whose slices hold `mine` entries, between `least` and `most`
+// (uniform), half of them at a time where the chunk ends among them; `between` runs after the
+// loads are issued.
+template <int LANES, int U, class Between>
+__device__ __forceinline__ void gather_eight(const char* Mc, uint32_t off, float w, uint32_t lane_off, int mine,
+                                             int least, int most, float4& acc, Between between) {
+  float4 x[8];
+  if (least >= U + 8) {
+    gather_load<LANES, U, 8, true>(Mc, off, lane_off, mine, x);
+    between();
+    gather_add<LANES, U, 8>(w, x, acc);
+  } else if (most > U + 4) {
+    if (least >= U + 4) gather_load<LANES, U, 4, true>(Mc, off, lane_off, mine, x);
+    else gather_load<LANES, U, 4, false>(Mc, off, lane_off, mine, x);
+    gather_load<LANES, U + 4, 4, false>(Mc, off, lane_off, mine, x + 4);
+    between();
+    gather_add<LANES, U, 8>(w, x, acc);
+  } else {
+    gather_load<LANES, U, 4, false>(Mc, off, lane_off, mine, x);
+    between();
+    gather_add<LANES, U, 4>(w, x, acc);
+  }
+}
+
+// The entries of one row whose source rows lie in one block.
+struct __attribute__((aligned(16))) Piece {
+  int64_t beg;
+  int32_t len, row;
+};
+
+constexpr int kWavesPerBlock = kBlockThreads / 64;
+
+// Rows longer than GCN_SPLIT_MIN (one block only): `groups` workgroups ahead of the others sum
+// one chunk of such a row per wavefront into part (pitch pw); k_finish_long adds a row's chunks.
+struct LongRows {
+  gcn_split sp;
+  float* part;
+  int64_t pw;
+  int32_t groups;
+};
+constexpr int kMaxRounds = 64 / kWavesPerBlock / kWavesPerBlock;  // one lane per item at most
+constexpr int kHub = 512;  // eight chunks: about 10 us for one wavefront
+
+// The finished columns of one row (every slice holds them; slice 0 writes): ReLU with its
+// bitmask, or the mask (mk, this lane's columns of it).
+template <int LANES, int EPI>
+__device__ __forceinline__ void store_row(const AggParams& p, int64_t row, float4 v, const float4& mk, const Lanes& L,
+                                          bool cok) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int c0 = L.c0;
+  if constexpr (EPI == AGG_RELU) {
+    if (p.relu_bits) {
+      // 1[v > 0] of this lane's columns, OR-ed over the eight lanes of a 32-column word
+      uint32_t bits = 0;
+      if (cok) {
+        bits |= v.x > 0.f ? 1u : 0u;
+        bits |= c0 + 1 < p.w && v.y > 0.f ? 2u : 0u;
+        bits |= c0 + 2 < p.w && v.z > 0.f ? 4u : 0u;
+        bits |= c0 + 3 < p.w && v.w > 0.f ? 8u : 0u;
+      }
+      bits = group_or<8>(bits << (c0 % 32));
+      if (L.slot == 0 && cok && L.lane % 8 == 0) p.relu_bits[row * p.ld_relu_bits + c0 / 32] = bits;
+    }
+    v = make_float4(fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f));
+  }
+  if constexpr (EPI == AGG_MASK) {
+    v.x = mk.x > 0.f ? v.x : 0.f;
+    v.y = mk.y > 0.f ? v.y : 0.f;
+    v.z = mk.z > 0.f ? v.z : 0.f;
+    v.w = mk.w > 0.f ? v.w : 0.f;
+  }
+  if (!cok || L.slot != 0) return;
+  float* out = p.Z + row * p.ldz + c0;
+  if (c0 + 4 <= p.w) {
+    // written once and not read by this kernel: L2 is left to the gathered rows
+    const f32x4 o = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(out));
+  } else {
+    out[0] = v.x;
+    if (c0 + 1 < p.w) out[1] = v.y;
+    if (c0 + 2 < p.w) out[2] = v.z;
+  }
+}
+
+// Workgroup b's wavefront w sums the pieces of rows 4 b + w, 4 b + w + nwaves, ... (`rounds` of
+// them; in processing order when blocked, so that rows of like length run together).  A piece
+// of more than kHub entries is shared: each of the four wavefronts of its workgroup sums a
+// quarter, and the quarters meet in LDS.  Which pieces are shared depends on the piece alone, so
+// the results do not depend on the order.
+template <int LANES, int EPI>
+__global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, const Piece* pieces, int32_t block,
+                                                               int32_t nblock, int32_t rounds, LongRows lr) {
+  constexpr int SL = 64 / LANES;
+  __shared__ __attribute__((aligned(16))) float s_part[2][kWavesPerBlock][4 * LANES];
+  Lanes L;
+  L.gw = 64;
+  L.lig = threadIdx.x & 63;
+  L.slot = L.lig / LANES;
+  L.lane = L.lig & (LANES - 1);
+  L.c0 = ((int)blockIdx.y * LANES + L.lane) * 4;
+  const bool cok = L.c0 < p.w;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  const char* Mc = reinterpret_cast<const char*>(p.M);
+  const uint32_t lane_off = cok ? 4u * (uint32_t)L.c0 : 0u;  // lanes past the width re-read column 0 (not used)
+  const uint32_t pitch = 4u * (uint32_t)p.ldm;
+  const bool first = block == 0, last = block == nblock - 1;
+
+  // Lane 4 r + q holds the piece of round r, wavefront q: every wavefront knows all of them.
+  const bool chunks = (int)blockIdx.x < lr.groups;
+  const int64_t nwaves = (int64_t)((int)gridDim.x - lr.groups) * kWavesPerBlock;
+  const int64_t hi = (int64_t)((int)blockIdx.x - (chunks ? 0 : lr.groups)) * kWavesPerBlock + L.lig % kWavesPerBlock +
+                     (int64_t)(L.lig / kWavesPerBlock) * nwaves;
+  Piece h{0, 0, -1};
+  if (chunks) {
+    rounds = 1;
+    if (L.lig < kWavesPerBlock && hi < lr.sp.n_chunk) {
+      const int64_t ch = lr.sp.order ? lr.sp.order[hi] : hi;
+      const int32_t o = lr.sp.owner[ch], row = lr.sp.rows[o];
+      h.beg = p.row_ptr[row] + (ch - lr.sp.first[o]) * (int64_t)GCN_SPLIT_CHUNK;
+      const int64_t left = p.row_ptr[row + 1] - h.beg;
+      h.len = (int)(left < GCN_SPLIT_CHUNK ? left : GCN_SPLIT_CHUNK);
+      h.row = (int)ch;
+    }
+  } else if (L.lig < kWavesPerBlock * rounds && hi < p.n) {
+    if (nblock > 1) {
+      h = pieces[(int64_t)block * p.n + hi];
+    } else {
+      const int64_t beg = p.row_ptr[hi], end = p.row_ptr[hi + 1];
+      if (lr.groups == 0 || end - beg <= GCN_SPLIT_MIN) h = Piece{beg, (int32_t)(end - beg), (int32_t)hi};
+    }
+  }
+  const uint64_t hubs = chunks ? 0 : __ballot(h.len > kHub);
+  // Lane t then takes this wavefront's item t: its own piece of a round, or its quarter of a
+  // shared one (kind: the wavefront that finishes it, or -1).  Every wavefront has the shared
+  // items in the same order, with one barrier each.
+  int nitems = rounds, src = kWavesPerBlock * L.lig + wave, kind = -1;
+  if (hubs) {
+    nitems = 0;
+    src = 0;
+    for (int r = 0; r < rounds; ++r) {
+      const uint32_t shared = (uint32_t)(hubs >> (kWavesPerBlock * r)) & ((1u << kWavesPerBlock) - 1);
+      for (int q = 0; q < kWavesPerBlock; ++q) {
+        if (!((shared >> q) & 1) && q != wave) continue;
+        if (L.lig == nitems) {
+          src = kWavesPerBlock * r + q;
+          kind = (shared >> q) & 1 ? q : -1;
+        }
+        ++nitems;
+      }
+    }
+  }
+  const int h_row = __shfl(h.row, src, 64);
+  int h_len = __shfl(h.len, src, 64);
+  int64_t h_beg = __shfl(h.beg, src, 64);
+  if (kind >= 0) {
+    const int part = (h_len + kWavesPerBlock - 1) / kWavesPerBlock;
+    const int lo = part * wave < h_len ? part * wave : h_len;
+    h_beg += lo;
+    h_len = h_len - lo < part ? h_len - lo : part;
+  }
+
+  // Epilogue inputs that need no waiting for at a row's end: the bias of this lane's columns,
+  // the mean's factor of the item's row.
+  float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (EPI != AGG_SOFTMAX && last && p.bias && cok) {
+    bias.x = p.bias[L.c0];
+    if (L.c0 + 1 < p.w) bias.y = p.bias[L.c0 + 1];
+    if (L.c0 + 2 < p.w) bias.z = p.bias[L.c0 + 2];
+    if (L.c0 + 3 < p.w) bias.w = p.bias[L.c0 + 3];
+  }
+  const float h_scale = EPI != AGG_SOFTMAX && last && !chunks && h_row >= 0 ? row_scale(p, h_row) : 1.f;
+
+  // The entries are requested two chunks ahead of the gathers: a chunk's indices come from
+  // behind the L2, its gathers mostly from it.  Every item has at least one (empty) chunk.
+  int f_item = 0, f_done = 0;
+  auto fetch = [&](int& j, float& w) __attribute__((always_inline)) {
+    j = 0;
+    w = 0.f;
+    if (f_item >= nitems) return;
+    const int f_len = __builtin_amdgcn_readlane(h_len, f_item);
+    const uint32_t blo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)h_beg, f_item);
+    const uint32_t bhi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)h_beg >> 32), f_item);
+    const int64_t base = (int64_t)(((uint64_t)bhi << 32) | blo) + f_done;
+    // the chunk's entries in SL runs, one per slice
+    const int cnt = f_len - f_done < 64 ? f_len - f_done : 64;
+    const int run = (cnt + SL - 1) / SL;
+    const int at = L.slot * run + L.lane;
+    if (L.lane < run && at < cnt) {
+      j = p.col[base + at];
+      if (p.kind == AGG_W_VAL) w = p.val[base + at];
+    }
+    f_done += 64;
+    if (f_done >= f_len) {
+      ++f_item;
+      f_done = 0;
+    }
+  };
+  int j0, j1;
+  float w0, w1;
+  fetch(j0, w0);
+  fetch(j1, w1);
+  // The loss epilogue (row maximum, exponentials, three slice reductions, loss and gradient row)
+  // costs every slice the same instructions: slice s keeps the sums of one row, and SL rows are
+  // finished at once (rows in one panel only; wider ones by k_finish_softmax).
+  float4 keep = make_float4(0.f, 0.f, 0.f, 0.f);
+  int keep_row = -1, kept = 0;
+  auto finish_kept = [&]() {
+    finish_row<LANES, 4, EPI, true>(p, keep_row, keep, L, cok, keep_row >= 0);
+    keep_row = -1;
+    kept = 0;
+  };
+  int parity = 0;
+  for (int t = 0; t < nitems; ++t) {
+    const int row = __builtin_amdgcn_readlane(h_row, t);
+    const int len = __builtin_amdgcn_readlane(h_len, t);
+    const int fin = __builtin_amdgcn_readlane(kind, t);
+    const bool mine = row >= 0 && (fin < 0 || fin == wave);
+    float* z = (chunks ? lr.part + row * lr.pw : p.Z + (int64_t)(row < 0 ? 0 : row) * p.ldz) + L.c0;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 part = acc, mk = acc;
+    if (!first && cok && L.slot == 0 && mine) part = *reinterpret_cast<const float4*>(z);
+    if (EPI == AGG_MASK && last && !chunks && cok && L.slot == 0 && mine)
+      mk = *reinterpret_cast<const float4*>(p.mask + (int64_t)row * p.ldmask + L.c0);
+    int done = 0;
+    do {
+      const int cnt = len - done < 64 ? len - done : 64;
+      const int run = (cnt + SL - 1) / SL;
+      const int left = cnt - L.slot * run;
+      const int have = left < run ? left : run;
+      const int tail = cnt - (SL - 1) * run, least = tail < 0 ? 0 : tail;
+      const uint32_t off = (uint32_t)j0 * pitch;
+      float w = w0;
+      if (p.kind != AGG_W_VAL)
+        w = L.lane < have ? (p.kind == AGG_W_COLMEAN ? 1.f / (float)p.deg[j0] : 1.f) : 0.f;
+      j0 = j1;
+      w0 = w1;
+      gather_eight<LANES, 0>(Mc, off, w, lane_off, have, least, run, acc,
+                             [&]() __attribute__((always_inline)) { fetch(j1, w1); });
+      if constexpr (LANES > 8)
+        if (run > 8) gather_eight<LANES, 8>(Mc, off, w, lane_off, have, least, run, acc, [] {});
+      if constexpr (LANES > 16) {
+        if (run > 16) gather_eight<LANES, 16>(Mc, off, w, lane_off, have, least, run, acc, [] {});
+        if (run > 24) gather_eight<LANES, 24>(Mc, off, w, lane_off, have, least, run, acc, [] {});
+      }
+      done += 64;
+    } while (done < len);
+    for (int o = LANES; o < 64; o <<= 1) Vec<4>::add_xor(acc, o, 64);
+    if (fin >= 0) {
+      float* sp = s_part[parity][0] + 4 * L.lane;
+      parity ^= 1;
+      if (L.slot == 0) *reinterpret_cast<float4*>(sp + wave * 4 * LANES) = acc;
+      __syncthreads();  // every wavefront has the same shared items
+      if (!mine) continue;
+      acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int q = 0; q < kWavesPerBlock; ++q) Vec<4>::add(acc, *reinterpret_cast<const float4*>(sp + q * 4 * LANES));
+    }
+    if (!mine) continue;
+    Vec<4>::add(acc, part);
+    if (!last || chunks || (EPI == AGG_SOFTMAX && gridDim.y > 1)) {
+      if (cok && L.slot == 0) *reinterpret_cast<float4*>(z) = acc;
+      continue;
+    }
+    if constexpr (EPI == AGG_SOFTMAX) {
+      if (L.slot == kept) {
+        keep = acc;
+        keep_row = row;
+      }
+      if (++kept == SL) finish_kept();
+      continue;
+    }
+    const float sc = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(h_scale), t));
+    float4 v = make_float4(sc * acc.x + bias.x, sc * acc.y + bias.y, sc * acc.z + bias.z, sc * acc.w + bias.w);
+    store_row<LANES, EPI>(p, row, v, mk, L, cok);
+  }
+  if constexpr (EPI == AGG_SOFTMAX)
+    if (kept > 0) finish_kept();
+}
+
+// One slice per long row: its chunk sums in chunk order, then the epilogue.
+template <int LANES, int EPI>
+__global__ void __launch_bounds__(kBlockThreads) k_finish_long(AggParams p, LongRows lr) {
+  Lanes L;
+  L.gw = LANES;
+  L.lig = threadIdx.x & (LANES - 1);
+  L.slot = 0;
+  L.lane = L.lig;
+  L.c0 = ((int)blockIdx.y * LANES + L.lane) * 4;
+  const int64_t o = ((int64_t)blockIdx.x * kBlockThreads + threadIdx.x) / LANES;
+  if (o >= lr.sp.n_long) return;
+  const bool cok = L.c0 < p.w;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (cok)
+    for (int64_t ch = lr.sp.first[o]; ch < lr.sp.first[o + 1]; ++ch)
+      Vec<4>::add(acc, *reinterpret_cast<const float4*>(lr.part + ch * lr.pw + L.c0));
+  const int64_t row = lr.sp.rows[o];
+  if (EPI == AGG_SOFTMAX && gridDim.y > 1) {
+    if (cok) *reinterpret_cast<float4*>(p.Z + row * p.ldz + L.c0) = acc;
+  } else {
+    finish_row<LANES, 4, EPI>(p, row, acc, L, cok);
+  }
+}
+
+// pieces[b * n + i]: the entries of the i-th row in processing order whose source rows lie in
+// block b.  Each search starts at the end before it, so the pieces make up the row whatever the
+// order of its columns; ascending ones (gcn_build_csr) make each block's gathers stay in it.
+__global__ void __launch_bounds__(256) k_block_pieces(int32_t n, const int64_t* row_ptr, const int32_t* col,
+                                                      const int32_t* order, int32_t rows, int32_t nblock,
+                                                      Piece* pieces) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int32_t row = order ? order[i] : (int32_t)i;
+  const int64_t end = row_ptr[row + 1];
+  int64_t lo = row_ptr[row];
+  for (int32_t b = 0; b < nblock; ++b) {
+    const int64_t beg = lo;
+    int64_t hi = end;
+    if (b + 1 < nblock) {
+      const int64_t bound = (int64_t)(b + 1) * rows;
+      while (lo < hi) {
+        const int64_t mid = lo + (hi - lo) / 2;
+        if (col[mid] < bound) lo = mid + 1;
+        else hi = mid;
+      }
+    } else {
+      lo = end;
+    }
+    pieces[(int64_t)b * n + i] = Piece{beg, (int32_t)(lo - beg), row};
+  }
+}
+
+// The loss epilogue over the finished sums in Z (a whole row per slice), where a row takes
+// several panels.
+template <int LANES>
+__global__ void __launch_bounds__(kBlockThreads) k_finish_softmax(AggParams p) {
+  Lanes L;
+  L.gw = LANES;
+  L.lig = threadIdx.x & (LANES - 1);
+  L.slot = 0;
+  L.lane = L.lig;
+  L.c0 = 4 * L.lane;
+  const int64_t row = ((int64_t)blockIdx.x * kBlockThreads + threadIdx.x) / LANES;
+  if (row >= p.n) return;
+  const bool cok = L.c0 < p.w;
+  const float4 acc = cok ? *reinterpret_cast<const float4*>(p.Z + row * p.ldz + L.c0) : make_float4(0.f, 0.f, 0.f, 0.f);
+  finish_row<LANES, 4, AGG_SOFTMAX>(p, row, acc, L, cok);
+}
+
+template <int LANES, int EPI>
+gcn_status run_blocks(const AggParams& p, const BlockedPlan& b, const Piece* pieces, const LongRows& lr, hipStream_t s) {
+  const int64_t panels = ceil_div(p.w, 4 * LANES);
+  // rows per wavefront: more hide the start of each (offsets, first entries), fewer fill the
+  // chip on small graphs and keep its end short (2 against 1 and 4: within 2 % on large ones)
+  const int most = b.nblock > 1 || EPI == AGG_SOFTMAX ? kMaxRounds : 2;
+  const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(most, (int64_t)p.n * panels / 32768));
+  const dim3 grid((unsigned)(lr.groups + ceil_div(p.n, (int64_t)rounds * kWavesPerBlock)), (unsigned)panels);
+  for (int32_t c = 0; c < b.nblock; ++c) {
+    if (c == b.nblock - 1)
+      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI>), grid, dim3(kBlockThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
+    else
+      hipLaunchKernelGGL((k_agg_blocked<LANES, AGG_NONE>), grid, dim3(kBlockThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
+    GCN_TRY(check_launch("blocked aggregation"));
+  }
+  if (lr.groups > 0) {
+    hipLaunchKernelGGL((k_finish_long<LANES, EPI>), dim3((unsigned)ceil_div((int64_t)lr.sp.n_long * LANES, kBlockThreads), (unsigned)panels),
+                       dim3(kBlockThreads), 0, s, p, lr);
+    GCN_TRY(check_launch("long rows"));
+  }
+  return GCN_OK;
+}
+
+template <int LANES>
+gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* pieces, const LongRows& lr, hipStream_t s) {
+  switch (p.epi) {
+    case AGG_NONE: return run_blocks<LANES, AGG_NONE>(p, b, pieces, lr, s);
+    case AGG_RELU: return run_blocks<LANES, AGG_RELU>(p, b, pieces, lr, s);
+    case AGG_MASK: return run_blocks<LANES, AGG_MASK>(p, b, pieces, lr, s);
+    default: break;
+  }
+  GCN_TRY((run_blocks<LANES, AGG_SOFTMAX>(p, b, pieces, lr, s)));
+  const int64_t need = ceil_div(p.w, 4);
+  if (need <= LANES) return GCN_OK;
+  auto finish = [&](auto ln) {
+    constexpr int LN = decltype(ln)::value;
+    hipLaunchKernelGGL(k_finish_softmax<LN>, dim3((unsigned)ceil_div((int64_t)p.n * LN, kBlockThreads)),
+                       dim3(kBlockThreads), 0, s, p);
+    return check_launch("softmax epilogue");
+  };
+  if (need <= 32) return finish(std::integral_constant<int, 32>{});
+  return finish(std::integral_constant<int, 64>{});
+}
+
+}  // namespace
+
+// Panel and block of an aggregation of n rows with nnz entries from src_rows rows of M (pitch
+// ldm), w columns.  All lines measured with Chung-Lu graphs of 5,000 to 1,000,000 rows and 8 to
+// 490 entries per row.
+//
+// Panel: one slice per row where the row fits (8 lanes up to 32 columns, 16 up to 64, 32 above);
+// wider rows that start at line boundaries take 64-column panels of two lines instead (width
+// 256, 169,343 rows: 306 us against 335; RMAT 2^21 rows 7,170 against 7,718), since half of the
+// panel fits the L2 twice; where rows are not line-aligned a narrower panel would fetch its edge
+// lines twice (width 100, 2,449,029 rows: 8,790 us in one panel, 12,900 in two).  32-column
+// panels pay where rows are gathered often and M is between the L2's size and a few times that
+// (100,000 rows of 64: 564 us against 671; 50,000 of 32: 145 against 152; of 8: 106 against 63).
+//
+// Blocks: 6 MB panels of M (R1) where a row has 24 entries per block, else 12 MB ones (R2) where
+// it has 24 (100,000 rows of 128 entries, width 256: 957 us with R1, 1,047 unblocked; 200,000 of
+// 128: 2,429 with R2, 2,713 unblocked; of 64: 1,594 against 1,416).  With 32 lanes the entries
+// are twice the bytes and 12 suffice for R2 (200,000 of 128, width 100: 1,205 against 1,612).
+// Rows of one line (8 lanes) gain from larger blocks alone, and from 2^17 rows on (200,000 of
+// 128, width 24: 406 against 464; 100,000 of 128: 203 against 176).
+BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w, int64_t ldm, bool may_block) {
+  BlockedPlan b{};
+  if (n <= 0 || nnz < 0 || src_rows <= 0 || w <= 16 || 4 * src_rows * ldm > (int64_t)UINT32_MAX) return b;
+  const bool lines = ldm % 32 == 0;
+  b.lanes = w <= 32 ? 8 : (w <= 64 || lines ? 16 : 32);
+  b.nblock = 1;
+  auto entries = [&](int64_t rows) { return (double)nnz / ((double)n * (double)ceil_div(src_rows, rows)); };
+  if (may_block && src_rows <= INT32_MAX) {
+    const int64_t r1 = 24576 * 16 / b.lanes, r2 = 2 * r1;
+    int64_t rows = 0;
+    if (b.lanes == 8) {
+      if (src_rows >= (1 << 17) && entries(r1) >= 24) rows = r1;
+    } else if (entries(r1) >= 24) {
+      rows = r1;
+    } else if (entries(r2) >= (b.lanes == 32 ? 12 : 24)) {
+      rows = r2;
+    }
+    if (rows > 0 && src_rows > rows) {
+      b.rows = (int32_t)rows;
+      b.nblock = (int32_t)ceil_div(src_rows, rows);
+      return b;
+    }
+  }
+  // M in the L2 as it is (the weight of a sparse first layer): fewer passes over the entries
+  if (w > 64 && n >= 32768 && 4 * src_rows * ldm <= (3 << 20)) b.lanes = 32;
+  if (lines && w > 64 && nnz >= 32 * n && src_rows >= 32768 && src_rows <= 400000) b.lanes = 8;
+  return b;
+}
+
+size_t agg_blocked_workspace(const BlockedPlan& b, int64_t n) {
+  return b.nblock > 1 ? sizeof(Piece) * (size_t)n * (size_t)b.nblock : 0;
+}
+
+gcn_status launch_agg_blocked(const AggParams& p, const BlockedPlan& b, const gcn_split* split, void* ws, hipStream_t s) {
+  Piece* pieces = nullptr;
+  LongRows lr{};
+  if (b.nblock > 1) {
+    pieces = static_cast<Piece*>(ws);
+    hipLaunchKernelGGL(k_block_pieces, dim3((unsigned)ceil_div(p.n, 256)), dim3(256), 0, s, p.n, p.row_ptr, p.col, p.order,
+                       b.rows, b.nblock, pieces);
+    GCN_TRY(check_launch("row pieces"));
+  } else if (has_split(split)) {
+    lr.sp = *split;
+    lr.part = static_cast<float*>(ws);
+    lr.pw = round_up(p.w, 4);
+    lr.groups = (int32_t)ceil_div(split->n_chunk, kWavesPerBlock);
+  }
+  switch (b.lanes) {
+    case 8: return run_lanes<8>(p, b, pieces, lr, s);
+    case 16: return run_lanes<16>(p, b, pieces, lr, s);
+    default: return run_lanes<32>(p, b, pieces, lr, s);
+  }
+}
+
+}  // namespace gcn

@@ -1,5 +1,5 @@
 // agg_device.h -- device-side building blocks of the row-parallel sparse products
-// (included by the aggregation kernels and the fused aggregate-then-transform kernel).
+// (included by the aggregation kernels).
 //
 // A slice of LANES lanes covers a row's columns, VEC consecutive columns per lane;
 // `slots` slices share a row and take every slots-th entry; UNR neighbour-row loads
@@ -154,6 +154,103 @@ __device__ __forceinline__ typename Vec<VEC>::T accumulate(const AggParams& p, i
   return acc;
 }
 
+// Bias and epilogue of one row.  Every slice of the group holds the row's total and
+// slice 0 writes; with OWN, each slice holds a row of its own (own: that row exists and
+// is finished here) and writes it.
+template <int LANES, int VEC, int EPI, bool OWN = false>
+__device__ __forceinline__ void finish_row(const AggParams& p, int64_t row, const typename Vec<VEC>::T& acc,
+                                           const Lanes& L, bool cok, bool own = true) {
+  using V = Vec<VEC>;
+  const int c0 = L.c0;
+  const bool writer = OWN ? own : L.slot == 0;
+  const float sc = own ? row_scale(p, row) : 1.f;
+  float z[VEC];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) {
+    const int c = c0 + i;
+    z[i] = sc * V::get(acc, i);
+    if (p.bias && c < p.w) z[i] += p.bias[c];
+  }
+  if constexpr (EPI == AGG_SOFTMAX) {
+    // whole logits row is held by each slice (w <= LANES * VEC); slice 0 writes
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+      if (c0 + i < p.w) mx = fmaxf(mx, z[i]);
+    mx = group_max<LANES>(mx);
+    float e[VEC];
+    float se = 0.f;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      e[i] = (c0 + i < p.w) ? expf(z[i] - mx) : 0.f;
+      se += e[i];
+    }
+    se = group_sum<LANES>(se);
+    const int y = own ? p.labels[row] : -1;
+    float zy = 0.f;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+      if (c0 + i == y) zy = z[i];
+    zy = group_sum<LANES>(zy);
+    if (!writer) return;
+    if (L.lane == 0) p.row_loss[row] = (logf(se) + mx) - zy;
+    if (!cok) return;
+    const float inv_se = 1.f / se;
+    float gv[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) gv[i] = (e[i] * inv_se - (c0 + i == y ? 1.f : 0.f)) * p.inv_n;
+    float* out = p.Z + row * p.ldz + c0;
+    float* lg = p.logits ? p.logits + row * p.ldl + c0 : nullptr;
+    if (VEC == 4 && c0 + 4 <= p.w) {
+      *reinterpret_cast<float4*>(out) = make_float4(gv[0], gv[VEC > 1 ? 1 : 0], gv[VEC > 2 ? 2 : 0],
+                                                    gv[VEC > 3 ? 3 : 0]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i)
+        if (c0 + i < p.w) out[i] = gv[i];
+    }
+    if (lg) {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i)
+        if (c0 + i < p.w) lg[i] = z[i];
+    }
+  } else {
+    if constexpr (EPI == AGG_RELU) {
+      if (p.relu_bits) {
+        // 1[z > 0] of this lane's columns, OR-ed over the lanes of one 32-column word
+        // (every lane of the group takes part before any leaves)
+        constexpr int kWordLanes = LANES < 32 / VEC ? LANES : 32 / VEC;
+        uint32_t bits = 0;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i)
+          if (c0 + i < p.w && z[i] > 0.f) bits |= 1u << ((c0 + i) % 32);
+        bits = group_or<kWordLanes>(bits);
+        if (writer && c0 < p.w && L.lane % kWordLanes == 0) p.relu_bits[row * p.ld_relu_bits + c0 / 32] = bits;
+      }
+    }
+    if (!cok || !writer) return;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      if constexpr (EPI == AGG_RELU) z[i] = fmaxf(z[i], 0.f);
+      if constexpr (EPI == AGG_MASK) {
+        const int c = c0 + i;
+        if (c < p.w) z[i] = p.mask[row * p.ldmask + c] > 0.f ? z[i] : 0.f;
+      }
+    }
+    float* out = p.Z + row * p.ldz + c0;
+    if (VEC == 4 && c0 + 4 <= p.w) {
+      // written once and not read by this kernel: a non-temporal store leaves L2 to the
+      // gathered rows
+      typedef float f32x4 __attribute__((ext_vector_type(4)));
+      const f32x4 o = {z[0], z[VEC > 1 ? 1 : 0], z[VEC > 2 ? 2 : 0], z[VEC > 3 ? 3 : 0]};
+      __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(out));
+    } else {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i)
+        if (c0 + i < p.w) out[i] = z[i];
+    }
+  }
+}
 
 }  // namespace
 }  // namespace gcn

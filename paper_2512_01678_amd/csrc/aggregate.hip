@@ -36,104 +36,6 @@ namespace {
 
 constexpr int kBlock = 256;
 
-// Bias and epilogue of one row.  Every slice of the group holds the row's total and
-// slice 0 writes; with OWN, each slice holds a row of its own (own: that row exists and
-// is finished here) and writes it.
-template <int LANES, int VEC, int EPI, bool OWN = false>
-__device__ __forceinline__ void finish_row(const AggParams& p, int64_t row, const typename Vec<VEC>::T& acc,
-                                           const Lanes& L, bool cok, bool own = true) {
-  using V = Vec<VEC>;
-  const int c0 = L.c0;
-  const bool writer = OWN ? own : L.slot == 0;
-  const float sc = own ? row_scale(p, row) : 1.f;
-  float z[VEC];
-#pragma unroll
-  for (int i = 0; i < VEC; ++i) {
-    const int c = c0 + i;
-    z[i] = sc * V::get(acc, i);
-    if (p.bias && c < p.w) z[i] += p.bias[c];
-  }
-  if constexpr (EPI == AGG_SOFTMAX) {
-    // whole logits row is held by each slice (w <= LANES * VEC); slice 0 writes
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i)
-      if (c0 + i < p.w) mx = fmaxf(mx, z[i]);
-    mx = group_max<LANES>(mx);
-    float e[VEC];
-    float se = 0.f;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-      e[i] = (c0 + i < p.w) ? expf(z[i] - mx) : 0.f;
-      se += e[i];
-    }
-    se = group_sum<LANES>(se);
-    const int y = own ? p.labels[row] : -1;
-    float zy = 0.f;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i)
-      if (c0 + i == y) zy = z[i];
-    zy = group_sum<LANES>(zy);
-    if (!writer) return;
-    if (L.lane == 0) p.row_loss[row] = (logf(se) + mx) - zy;
-    if (!cok) return;
-    const float inv_se = 1.f / se;
-    float gv[VEC];
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) gv[i] = (e[i] * inv_se - (c0 + i == y ? 1.f : 0.f)) * p.inv_n;
-    float* out = p.Z + row * p.ldz + c0;
-    float* lg = p.logits ? p.logits + row * p.ldl + c0 : nullptr;
-    if (VEC == 4 && c0 + 4 <= p.w) {
-      *reinterpret_cast<float4*>(out) = make_float4(gv[0], gv[VEC > 1 ? 1 : 0], gv[VEC > 2 ? 2 : 0],
-                                                    gv[VEC > 3 ? 3 : 0]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < VEC; ++i)
-        if (c0 + i < p.w) out[i] = gv[i];
-    }
-    if (lg) {
-#pragma unroll
-      for (int i = 0; i < VEC; ++i)
-        if (c0 + i < p.w) lg[i] = z[i];
-    }
-  } else {
-    if constexpr (EPI == AGG_RELU) {
-      if (p.relu_bits) {
-        // 1[z > 0] of this lane's columns, OR-ed over the lanes of one 32-column word
-        // (every lane of the group takes part before any leaves)
-        constexpr int kWordLanes = LANES < 32 / VEC ? LANES : 32 / VEC;
-        uint32_t bits = 0;
-#pragma unroll
-        for (int i = 0; i < VEC; ++i)
-          if (c0 + i < p.w && z[i] > 0.f) bits |= 1u << ((c0 + i) % 32);
-        bits = group_or<kWordLanes>(bits);
-        if (writer && c0 < p.w && L.lane % kWordLanes == 0) p.relu_bits[row * p.ld_relu_bits + c0 / 32] = bits;
-      }
-    }
-    if (!cok || !writer) return;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-      if constexpr (EPI == AGG_RELU) z[i] = fmaxf(z[i], 0.f);
-      if constexpr (EPI == AGG_MASK) {
-        const int c = c0 + i;
-        if (c < p.w) z[i] = p.mask[row * p.ldmask + c] > 0.f ? z[i] : 0.f;
-      }
-    }
-    float* out = p.Z + row * p.ldz + c0;
-    if (VEC == 4 && c0 + 4 <= p.w) {
-      // written once and not read by this kernel: a non-temporal store leaves L2 to the
-      // gathered rows
-      typedef float f32x4 __attribute__((ext_vector_type(4)));
-      const f32x4 o = {z[0], z[VEC > 1 ? 1 : 0], z[VEC > 2 ? 2 : 0], z[VEC > 3 ? 3 : 0]};
-      __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(out));
-    } else {
-#pragma unroll
-      for (int i = 0; i < VEC; ++i)
-        if (c0 + i < p.w) out[i] = z[i];
-    }
-  }
-}
-
 // Every row whose length is at most skip_over (all rows when there is no split plan).
 // One group per row; the hardware overlaps many resident wavefronts, which hides
 // the per-row chain of dependent loads better than prefetching across rows does.
@@ -290,37 +192,6 @@ bool use_vec4(const AggParams& p) {
 }
 
 }  // namespace
-
-gcn_status launch_aggregate_long_rows(const AggParams& p, const gcn_split* split, void* ws, hipStream_t s) {
-  if (!has_split(split) || p.w == 0) return GCN_OK;
-  if (!use_vec4(p) || p.epi != AGG_NONE)
-    return fail(GCN_E_UNSUPPORTED, "long-row aggregation: needs 16-byte rows and no epilogue");
-  int lanes = 1;
-  while (lanes < ceil_div(p.w, 4) && lanes < 64) lanes <<= 1;
-  const int slots = std::min(64 / lanes, 16);
-  const int gw = lanes * slots;
-  const unsigned gy = (unsigned)ceil_div(p.w, lanes * 4);
-  const int64_t pw = round_up(p.w, 4);
-  float* part = static_cast<float*>(ws);
-  auto run = [&](auto tag) -> gcn_status {
-    constexpr int LN = decltype(tag)::value;
-    hipLaunchKernelGGL((k_chunks<LN, 4>), dim3((unsigned)ceil_div(split->n_chunk, kBlock / gw), gy), dim3(kBlock),
-                       0, s, p, *split, slots, part, pw);
-    GCN_TRY(check_launch("aggregate chunks"));
-    hipLaunchKernelGGL((k_combine<LN, 4, AGG_NONE>), dim3((unsigned)ceil_div(split->n_long, kBlock / LN), gy),
-                       dim3(kBlock), 0, s, p, *split, 1, part, pw);
-    return check_launch("aggregate combine");
-  };
-  switch (lanes) {
-    case 1: return run(std::integral_constant<int, 1>{});
-    case 2: return run(std::integral_constant<int, 2>{});
-    case 4: return run(std::integral_constant<int, 4>{});
-    case 8: return run(std::integral_constant<int, 8>{});
-    case 16: return run(std::integral_constant<int, 16>{});
-    case 32: return run(std::integral_constant<int, 32>{});
-    default: return run(std::integral_constant<int, 64>{});
-  }
-}
 
 int agg_slots(int lanes, int64_t nnz, int64_t rows) { return pick_slots(lanes, nnz, rows); }
 
@@ -557,10 +428,29 @@ size_t aggregate_workspace(const gcn_split* split, int32_t w) {
   return sizeof(float) * (size_t)split->n_chunk * (size_t)round_up(w, 4);
 }
 
+size_t graph_aggregate_workspace(const gcn_graph* g, int32_t w, int64_t ldm) {
+  return std::max(aggregate_workspace(&g->split, w),
+                  agg_blocked_workspace(agg_blocked_plan(g->n, g->n, g->nnz, w, ldm, true), g->n));
+}
+
 gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* split, void* ws,
                             hipStream_t s) {
   if (p.n == 0 || p.w == 0) return GCN_OK;
   const bool vec4 = use_vec4(p);
+  char name[64];
+  snprintf(name, sizeof name, "%s_w%d", p.tag ? p.tag : "aggregate", p.w);
+  if (vec4 && p.src_rows > 0) {
+    // blocked sums rest in Z between the launches: not where the mask lies in it
+    const bool mask_in_z = p.epi == AGG_MASK && p.mask < p.Z + (int64_t)p.n * p.ldz &&
+                           p.Z < p.mask + (int64_t)p.n * p.ldmask;
+    const BlockedPlan b = agg_blocked_plan(p.n, p.src_rows, nnz, p.w, p.ldm, p.may_block && !mask_in_z);
+    if (b.nblock > 0 && (p.epi != AGG_SOFTMAX || p.w <= 256)) {
+      if (!ws && (b.nblock > 1 || has_split(split)))
+        return fail(GCN_E_INVALID, "aggregation: the workspace is missing");
+      ProfScope prof(name, p.w, p.n, nnz, s);
+      return launch_agg_blocked(p, b, split, ws, s);
+    }
+  }
   const int vec = vec4 ? 4 : 1;
   int need = (int)ceil_div(p.w, vec);
   // A slice spans at most 32 lanes (128 columns with 16-byte loads); wider rows take
@@ -589,8 +479,6 @@ gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* sp
   a.slots = pick_slots(lanes, nnz, p.n);
   a.chunk_slots = std::min(64 / lanes, 16);
   a.s = s;
-  char name[64];
-  snprintf(name, sizeof name, "%s_w%d", p.tag ? p.tag : "aggregate", p.w);
   ProfScope prof(name, p.w, p.n, nnz, s);
   return vec4 ? launch1<4>(a, lanes) : launch1<1>(a, lanes);
 }

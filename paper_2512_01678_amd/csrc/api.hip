@@ -111,17 +111,6 @@ int32_t resolve_order(const gcn_layer* L, bool x_sparse) {
   return af < 2 * (int64_t)L->f_out ? GCN_AGGREGATE_FIRST : GCN_TRANSFORM_FIRST;
 }
 
-// The fused aggregate-first kernel serves 32 < f_in <= 128 in bf16x6 mode when
-// GCN_AF_FUSED=1.  By default the layer runs as the aggregation followed by the
-// row-panel GEMM, measured faster (arxiv-like layer 0: 229 + 100 us against 347 us;
-// products-like 8.90 + 1.14 ms against 10.47 ms): the fused kernel's LDS and registers
-// leave the gathers fewer wavefronts per CU than the standalone aggregation has.
-bool af_fusable(int32_t f_in) {
-  const char* e = getenv("GCN_AF_FUSED");
-  if (!(e && e[0] == '1')) return false;
-  return gemm_bf16x6_mode() && f_in > 32 && f_in <= 128;
-}
-
 // The aggregator that carries gradients back: A_hat and A + I are symmetric; the
 // mean's transpose is (A + I) D^-1.
 int32_t agg_transpose(int32_t agg) {
@@ -148,6 +137,8 @@ AggParams graph_agg(const gcn_graph* g, int32_t w, const float* M, int64_t ldm, 
   p.ldz = ldz;
   p.epi = AGG_NONE;
   p.order = g->order;
+  p.src_rows = g->n;
+  p.may_block = true;
   return p;
 }
 
@@ -187,7 +178,7 @@ gcn_status loss_pass(int32_t n, const gcn_layer* L, const float* G, const float*
 
 // X_csr W of a sparse first layer: lane slices of each row gather a row of W per entry
 // (the aggregation kernel with the stored values of X).
-gcn_status launch_spmm_xw(int64_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col, const float* val,
+gcn_status launch_spmm_xw(int64_t n, int64_t f, int64_t nnz, const int64_t* row_ptr, const int32_t* col, const float* val,
                           const float* W, int64_t ldw, int32_t w, float* C, int64_t ldc, hipStream_t s) {
   AggParams p{};
   p.n = (int32_t)n;
@@ -200,6 +191,7 @@ gcn_status launch_spmm_xw(int64_t n, int64_t nnz, const int64_t* row_ptr, const 
   p.Z = C;
   p.ldz = ldc;
   p.epi = AGG_NONE;
+  p.src_rows = f;
   p.tag = "spmm_xw";
   return launch_aggregate(p, nnz, nullptr, nullptr, s);
 }
@@ -215,23 +207,18 @@ gcn_status layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* Hin, c
   if (bits_written) *bits_written = false;
   const bool want_bits = relu_bits && L->act == GCN_ACT_RELU;
   if (order == GCN_AGGREGATE_FIRST) {
-    // P = S H_in (kept for the backward pass), then H_out = act(P W + b): one fused
-    // kernel when the widths allow it (bf16x6 mode, linear S), else an aggregation and a
-    // GEMM.  The workspace covers both, so a size query made without buffers stays valid.
+    // P = S H_in (kept for the backward pass), then H_out = act(P W + b).
     // With the softmax cross-entropy, Z = P W + b goes through the loss epilogue of an
     // aggregation over the identity operator.
     const bool softmax = L->act == GCN_ACT_SOFTMAX_CE;
-    const bool fusable = af_fusable(L->f_in) && L->agg != GCN_AGG_MAX && !softmax;
-    size_t need = aggregate_workspace(&g->split, L->f_in);
-    if (fusable) need = std::max(need, agg_gemm_workspace(&g->split, L->f_in, L->f_out));
-    void* aws = a.take<char>((int64_t)need);
+    void* aws = a.take<char>((int64_t)graph_aggregate_workspace(g, L->f_in, L->ld_in));
     const int64_t ldz = gather_pitch(L->f_out);
     float* Zs = softmax ? a.take<float>((int64_t)n * ldz) : nullptr;
     int64_t* id_ptr = softmax ? a.take<int64_t>((int64_t)n + 1) : nullptr;
     int32_t* id_col = softmax ? a.take<int32_t>(n) : nullptr;
     float* row_loss = softmax ? a.take<float>(n) : nullptr;
     void* cws = softmax ? a.take<char>((int64_t)colsum_workspace(n, L->f_out)) : nullptr;
-    // H_out = P W (+ b) when the fused kernel does not run (split weight in the workspace)
+    // H_out = P W (+ b) (split weight in the workspace)
     GemmParams q = gemm(n, L->f_out, L->f_in, saved, L->ld_in, false, W, L->f_out, false, softmax ? Zs : Hout,
                         softmax ? ldz : L->ld_out);
     q.bias = b;
@@ -270,40 +257,30 @@ gcn_status layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* Hin, c
       return GCN_OK;
     }
     q.epi = L->act == GCN_ACT_RELU ? GEMM_RELU : GEMM_NONE;
-    const bool fused = fusable && agg_gemm_supported(L->f_in, L->ld_in, L->ld_in, Hin, saved);
-    if (want_bits && !fused && gemm_rows_supported(q)) {
+    if (want_bits && gemm_rows_supported(q)) {
       q.relu_bits = relu_bits;
       q.ld_relu_bits = relu_bits_words(L->f_out);
       if (bits_written) *bits_written = true;
     }
-    if (run && L->agg == GCN_AGG_MAX) {
-      GCN_TRY(launch_gemm(with_split(q, sj, nsj), gws, s));
-      return GCN_OK;
-    }
-    if (run) {
+    if (!run) return GCN_OK;
+    if (L->agg != GCN_AGG_MAX) {
       AggParams p = graph_agg(g, L->f_in, Hin, L->ld_in, saved, L->ld_in, L->agg);
-      if (fused) {
-        GCN_TRY(launch_agg_gemm(p, g->nnz, &g->split, W, L->f_out, L->f_out, b, L->act == GCN_ACT_RELU, Hout,
-                                L->ld_out, aws, s));
-      } else {
-        GCN_TRY(launch_aggregate(p, g->nnz, &g->split, aws, s));
-        GCN_TRY(launch_gemm(with_split(q, sj, nsj), gws, s));
-      }
+      GCN_TRY(launch_aggregate(p, g->nnz, &g->split, aws, s));
     }
-    return GCN_OK;
+    return launch_gemm(with_split(q, sj, nsj), gws, s);
   }
   // transform-first: M = H_in W (or X_csr W), then Z = A_hat M + b with the epilogue
   const int64_t ldm = gather_pitch(L->f_out);
   float* M = a.take<float>((int64_t)n * ldm);
   float* row_loss = L->act == GCN_ACT_SOFTMAX_CE ? a.take<float>(n) : nullptr;
   void* cws = L->act == GCN_ACT_SOFTMAX_CE ? a.take<char>((int64_t)colsum_workspace(n, L->f_out)) : nullptr;
-  void* aws = a.take<char>((int64_t)aggregate_workspace(&g->split, L->f_out));
+  void* aws = a.take<char>((int64_t)graph_aggregate_workspace(g, L->f_out, ldm));
   const GemmParams q = gemm(n, L->f_out, L->f_in, Hin, L->ld_in, false, W, L->f_out, false, M, ldm);
   void* gws = x ? nullptr : a.take<char>((int64_t)gemm_workspace(q));
   if (bits_written) *bits_written = want_bits;  // the aggregation epilogue writes them
   if (!run) return GCN_OK;
   if (x) {
-    GCN_TRY(launch_spmm_xw(n, x->nnz, x->row_ptr, x->col, x->val, W, L->f_out, L->f_out, M, ldm, s));
+    GCN_TRY(launch_spmm_xw(n, x->f, x->nnz, x->row_ptr, x->col, x->val, W, L->f_out, L->f_out, M, ldm, s));
   } else {
     GCN_TRY(launch_gemm(with_split(q, sj, nsj), gws, s));
   }
@@ -349,7 +326,7 @@ gcn_status layer_bwd(const gcn_graph* g, const gcn_layer* L, const float* G, con
     void* gws = a.take<char>((int64_t)gemm_workspace(dw));
     const int64_t ldt = gather_pitch(L->f_in);
     float* T = Gprev ? a.take<float>((int64_t)n * ldt) : nullptr;
-    void* aws = Gprev ? a.take<char>((int64_t)aggregate_workspace(&g->split, L->f_in)) : nullptr;
+    void* aws = Gprev ? a.take<char>((int64_t)graph_aggregate_workspace(g, L->f_in, ldt)) : nullptr;
     const GemmParams t = gemm(n, L->f_in, L->f_out, G, L->ld_out, false, W, L->f_out, true, T, ldt);
     void* tws = Gprev ? a.take<char>((int64_t)gemm_workspace(t)) : nullptr;
     if (!run) return GCN_OK;
@@ -376,7 +353,7 @@ gcn_status layer_bwd(const gcn_graph* g, const gcn_layer* L, const float* G, con
   float* Q = a.take<float>((int64_t)n * ldq);
   GemmParams dw = gemm(L->f_in, L->f_out, n, Hin, L->ld_in, true, Q, ldq, false, dW, L->f_out);
   void* gws = x ? nullptr : a.take<char>((int64_t)gemm_workspace(dw));
-  const size_t agg_need = std::max(aggregate_workspace(&g->split, L->f_out),
+  const size_t agg_need = std::max(graph_aggregate_workspace(g, L->f_out, L->ld_out),
                                    x && x->col_ptr ? spmm_xt_workspace(n, x->f, x->nnz, L->f_out, &x->csc_split)
                                                    : (size_t)0);
   void* aws = a.take<char>((int64_t)agg_need);
@@ -697,7 +674,7 @@ gcn_status gcn_aggregate(const gcn_graph* g, int32_t agg, int32_t w, const float
   if (epi < GCN_EPI_NONE || epi > GCN_EPI_MASK) return fail(GCN_E_INVALID, "gcn_aggregate: unknown epilogue");
   if (epi == GCN_EPI_MASK && (!d_mask || ldmask < w)) return fail(GCN_E_INVALID, "gcn_aggregate: mask missing");
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, aggregate_workspace(&g->split, w), "gcn_aggregate", &query));
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, graph_aggregate_workspace(g, w, ldm), "gcn_aggregate", &query));
   if (query) return GCN_OK;
   if (g->n > 0 && w > 0 && (!d_M || !d_Z)) return fail(GCN_E_INVALID, "gcn_aggregate: d_M and d_Z are required");
   AggParams p = graph_agg(g, w, d_M, ldm, d_Z, ldz, agg);
@@ -788,6 +765,7 @@ gcn_status gcn_spmm(int64_t nrows, int64_t nnz, const int64_t* d_ptr, const int3
   p.Z = d_C;
   p.ldz = ldc;
   p.epi = AGG_NONE;
+  p.src_rows = b_rows;
   p.tag = "spmm";
   return launch_aggregate(p, nnz, split, d_ws, stream);
 }
@@ -820,7 +798,7 @@ gcn_status gcn_spmm_xw(int32_t n, int32_t f, int64_t nnz, const int64_t* d_row_p
   if (n > 0 && w > 0 && (!d_row_ptr || (nnz > 0 && (!d_col || !d_val || !d_W)) || !d_C))
     return fail(GCN_E_INVALID, "gcn_spmm_xw: NULL argument");
   if (n == 0 || w == 0) return GCN_OK;
-  return launch_spmm_xw(n, nnz, d_row_ptr, d_col, d_val, d_W, ldw, w, d_C, ldc, stream);
+  return launch_spmm_xw(n, f, nnz, d_row_ptr, d_col, d_val, d_W, ldw, w, d_C, ldc, stream);
 }
 
 gcn_status gcn_column_sums(int64_t rows, int32_t w, const float* d_G, int64_t ldg, float* d_out,

@@ -102,12 +102,25 @@ struct AggParams {
   int64_t ld_relu_bits;    // words per row (>= ceil(w / 32))
   // order in which the main kernel takes the rows (n entries), or NULL for 0 .. n-1
   const int32_t* order;
+  int64_t src_rows;        // rows of M, or 0 (unknown)
+  bool may_block;          // ws has room for the blocked form (graph_aggregate_workspace)
 };
 // Words per row of a ReLU bitmask of width w.
 inline int64_t relu_bits_words(int32_t w) { return (w + 31) / 32; }
+// The form of 16-byte rows wider than 16 columns (agg_blocked.hip): panels of 4 * lanes columns;
+// nblock > 1: blocked by source rows, `rows` rows of M each; nblock == 0: not taken.
+struct BlockedPlan {
+  int lanes;
+  int32_t rows, nblock;
+};
+BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w, int64_t ldm, bool may_block);
+size_t agg_blocked_workspace(const BlockedPlan& b, int64_t n);
+gcn_status launch_agg_blocked(const AggParams& p, const BlockedPlan& b, const gcn_split* split, void* ws, hipStream_t s);
 // Z over all rows; rows longer than GCN_SPLIT_MIN go through the split plan when one
 // is given (its chunk sums live in ws, aggregate_workspace() bytes).
 size_t aggregate_workspace(const gcn_split* split, int32_t w);
+// The same for a graph of n nodes whose aggregations may be blocked (ldm: pitch of M).
+size_t graph_aggregate_workspace(const gcn_graph* g, int32_t w, int64_t ldm);
 gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* split, void* ws,
                             hipStream_t s);
 inline bool has_split(const gcn_split* sp) { return sp && sp->rows && sp->n_long > 0; }
@@ -144,17 +157,6 @@ gcn_status launch_partial_sum(const float* part, int64_t splits, int64_t m, int6
                               hipStream_t s);
 // Identity operator in CSR form: row_ptr[i] = i, col[i] = i.
 gcn_status launch_identity_csr(int32_t n, int64_t* row_ptr, int32_t* col, hipStream_t s);
-// Only the long rows of a split plan (chunk sums, then their combination), no epilogue.
-gcn_status launch_aggregate_long_rows(const AggParams& p, const gcn_split* split, void* ws, hipStream_t s);
-
-// Aggregate-first layer in one kernel: P = A_hat X (written to a.Z), H = act(P W + b),
-// in the bf16x6 arithmetic of the dense products.  W is f_in x f_out (pitch ldw).
-bool agg_gemm_supported(int32_t f_in, int64_t ldx, int64_t ldp, const float* X, const float* P);
-size_t agg_gemm_workspace(const gcn_split* split, int32_t f_in, int32_t f_out);
-gcn_status launch_agg_gemm(const AggParams& a, int64_t nnz, const gcn_split* split, const float* W,
-                           int64_t ldw, int32_t f_out, const float* bias, bool relu, float* H, int64_t ldh,
-                           void* ws, hipStream_t s);
-
 // split plan of the long rows of a compressed matrix with offsets ptr[0..nrows]
 size_t split_workspace(int64_t nrows);
 gcn_status build_split(const int64_t* ptr, int64_t nrows, gcn_split* sp, bool chunk_major, void* ws,

@@ -801,3 +801,56 @@ def test_gemm_bf16x6_matches_native_fp32(G, op, shape, monkeypatch):
         assert_mag_close(out[mode], ref, mag, f"{mode} {op} {shape}")
     worst = assert_mag_close(out["bf16x6"], out["fp32"], mag, f"bf16x6 vs fp32 {op} {shape}", rtol=2e-6)
     print(f"bf16x6 vs fp32 {op} {shape}: max |diff| / scale = {worst:.2e}")
+
+
+@pytest.mark.parametrize("n,e,blocked", [(30000, 1100000, True), (30000, 200000, False), (70, 400, False)])
+def test_wide_row_panels(G, orc, n, e, blocked):
+    """The panelled aggregation at the edges of its panels (32, 64 and 128 columns; pitches that
+    are and are not multiples of a line), for every weight kind and epilogue, unblocked and
+    blocked by source rows (two blocks of 24,576 and four of 12,288: at least 24 entries of an
+    average row in each), rows cut over four wavefronts (more than 512 entries) and, by the
+    split plan, over chunks (more than 4,096).  Tolerance: fp32 rounding relative to the sum of
+    |terms| of an element, as everywhere here.  The same sums come out bit for bit again and
+    without the row order."""
+    s, d = gs.chung_lu(n, e, seed=3, dmax=min(n // 4, 6000.0))
+    og, dg = orc.build_csr(n, s, d), G.build_csr(n, dev(s), dev(d))
+    plain = G.build_csr(n, dev(s), dev(d), order=False)
+    if n > 1000:
+        assert og.deg.max() > 512
+    if blocked:
+        assert og.nnz / (n * 3) >= 24 and dg.n_long > 0
+    rng = np.random.default_rng(e)
+    rows = np.unique(np.concatenate([rng.integers(0, n, 200), np.argsort(og.deg)[-20:], np.argsort(og.deg)[:20]]))
+    M = rng.standard_normal((n, 260)).astype(np.float32)
+    bias = rng.standard_normal(260).astype(np.float32)
+    mask = rng.standard_normal((n, 260)).astype(np.float32)
+    kinds = {"norm": G.AGG_NORM, "sum": G.AGG_SUM, "mean": G.AGG_MEAN, "mean_t": G.AGG_MEAN_T}
+    for w, ld in ((17, 20), (32, 32), (33, 48), (64, 64), (65, 68), (100, 100), (128, 128), (129, 132), (256, 256),
+                  (260, 288)):
+        for kind, epi in (("norm", G.EPI_NONE), ("norm", G.EPI_RELU), ("sum", G.EPI_MASK), ("mean", G.EPI_RELU),
+                          ("mean_t", G.EPI_NONE)):
+            Md, Kd = pitched(M[:, :w], ld), pitched(mask[:, :w], ld)
+            outs = []
+            for g in (dg, dg, plain):
+                Z = pitched(np.full((n, w), np.nan, np.float32), ld)
+                G.aggregate(g, Md, Z, bias=dev(bias[:w]), epi=epi, mask=Kd if epi == G.EPI_MASK else None,
+                            agg=kinds[kind])
+                outs.append(host(Z))
+            np.testing.assert_array_equal(outs[0], outs[1])
+            np.testing.assert_array_equal(outs[0], outs[2])
+            want, mag = orc.aggregate(og, M[:, :w], bias[:w], rows=rows, want_mag=True, kind="gcn" if kind == "norm" else kind)
+            if epi == G.EPI_RELU:
+                want = np.maximum(want, 0)
+            elif epi == G.EPI_MASK:
+                want = want * (mask[rows, :w] > 0)
+            assert_mag_close(outs[0][rows], want, mag, f"{kind} epi {epi} width {w} pitch {ld}")
+    # an infinity reaches exactly the rows that gather it
+    Mi = M[:, :64].copy()
+    Mi[7, 3] = np.inf
+    Z = pitched(np.zeros((n, 64), np.float32), 64)
+    G.aggregate(dg, pitched(Mi, 64), Z)
+    hit = np.zeros(n, bool)
+    hit[np.repeat(np.arange(n), og.deg)[og.col_idx == 7]] = True
+    got = host(Z)
+    np.testing.assert_array_equal(np.isinf(got[:, 3]), hit)
+    assert np.isfinite(np.delete(got, 3, axis=1)).all() and not np.isnan(got).any()
