@@ -492,7 +492,7 @@ gcn_status gcn_feature_stats(const float* d_X, int32_t n, int32_t f, int64_t ldx
   if (force_mode < -1 || force_mode > GCN_SPARSE) return fail(GCN_E_INVALID, "gcn_feature_stats: bad force_mode");
   const bool csc = x && x->col_ptr;
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, feature_stats_workspace(n, f, csc), "gcn_feature_stats", &query));
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, feature_stats_workspace(n, f, x != nullptr, csc), "gcn_feature_stats", &query));
   if (query) return GCN_OK;
   if (!info || (n > 0 && f > 0 && !d_X)) return fail(GCN_E_INVALID, "gcn_feature_stats: X and info are required");
   if (x && (!x->row_ptr || !x->col || !x->val || (csc && (!x->row || !x->cval))))

@@ -238,7 +238,8 @@ size_t build_csr_workspace(int32_t n, int64_t n_edges);
 gcn_status run_build_csr(int32_t n, int64_t n_edges, const int32_t* src, const int32_t* dst,
                          gcn_graph* g, void* ws, hipStream_t s);
 
-size_t feature_stats_workspace(int32_t n, int32_t f, bool want_csc);
+// views: X_csr is wanted too; want_csc: and X_csc.
+size_t feature_stats_workspace(int32_t n, int32_t f, bool views, bool want_csc);
 gcn_status run_feature_stats(const float* X, int32_t n, int32_t f, int64_t ldx, int32_t tau_num,
                              int32_t tau_den, int32_t force_mode, int64_t* row_nnz,
                              gcn_feature_info* info, gcn_sparse_x* x, void* ws, hipStream_t s);

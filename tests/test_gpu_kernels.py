@@ -854,3 +854,31 @@ def test_wide_row_panels(G, orc, n, e, blocked):
     got = host(Z)
     np.testing.assert_array_equal(np.isinf(got[:, 3]), hit)
     assert np.isfinite(np.delete(got, 3, axis=1)).all() and not np.isnan(got).any()
+
+
+@pytest.mark.parametrize("f,ld", [(1, 1), (31, 32), (33, 33), (128, 128), (257, 260), (1025, 1028), (4097, 4097),
+                                  (8200, 8200)])
+def test_feature_views_edges(G, orc, f, ld):
+    """Counts and both views, byte for byte, at the edges of the words (32 columns), of a
+    wavefront's turn (256 to 1,024 columns), of the column blocks (4,096) and of the row chunks
+    (64), sparse and dense rows (the views' two forms meet at one nonzero in 20), with rows of
+    more than 64 nonzeros, empty rows and columns, NaN, infinities and -0.0, and NaN in the
+    padding."""
+    rng = np.random.default_rng(f)
+    for n, p in ((1, 0.5), (64, 0.0), (65, 0.02), (130, 0.045), (200, 0.055), (63, 1.0)):
+        X = np.where(rng.random((n, f)) < p, rng.standard_normal((n, f)), 0.0).astype(np.float32)
+        X[n // 2, f // 2] = np.nan
+        X[0, f - 1] = -np.inf
+        X[n - 1, 0] = -0.0
+        Xd = pitched(X, ld)  # NaN in the padding
+        info, sx = G.feature_stats(Xd, materialize=True)
+        nnz = int((X != 0).sum())
+        assert info["nnz"] == nnz and sx.nnz == nnz
+        rp, col, val = orc.dense_to_csr(X)
+        cp, row, cval = orc.dense_to_csc(X)
+        np.testing.assert_array_equal(host(sx.row_ptr), rp)
+        np.testing.assert_array_equal(host(sx.col)[:nnz], col)
+        np.testing.assert_array_equal(host(sx.val)[:nnz].view(np.int32), val.astype(np.float32).view(np.int32))
+        np.testing.assert_array_equal(host(sx.col_ptr), cp)
+        np.testing.assert_array_equal(host(sx.row)[:nnz], row)
+        np.testing.assert_array_equal(host(sx.cval)[:nnz].view(np.int32), cval.astype(np.float32).view(np.int32))
