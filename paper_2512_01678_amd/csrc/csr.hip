@@ -4,43 +4,87 @@
 // neighbours plus itself, in a fixed (ascending) order so that the result is
 // canonical and bit-exact against any other correct construction.
 //
-//  1. count: every non-self input pair adds one raw entry to both endpoint rows;
-//     each row starts with its self entry (integer atomics: counts only).
-//  2. scan the raw counts into raw row offsets.
-//  3. fill: scatter both directions of each pair into the raw rows (the order
-//     within a row depends on scheduling; step 4 removes that dependence).
-//  4. sort + deduplicate each raw row in place, by row length:
-//       <= 64 entries    one wavefront, rank by cross-lane comparison;
+//  1. partition: both directions of every non-self pair go to the bucket of their row (2^s1
+//     rows each), then, bucket by bucket, to the sub-bucket (2^s2 rows, about 6,000 entries):
+//     counts in LDS, one scan, and a scatter whose open lines (one per bucket and workgroup)
+//     stay in the L2 until they are full.  No atomic leaves a CU.
+//  2. rows: one workgroup per sub-bucket counts its rows, adds each row's self entry and puts
+//     the columns into their rows in LDS (in memory where they do not fit); a wavefront sorts
+//     and deduplicates each row of up to 512 entries in registers (bitonic over lanes) and
+//     writes it to the row's raw place.  The order in which entries arrive depends on
+//     scheduling; the sort removes that dependence.
+//  3. longer rows in place:
 //       <= 4096 entries  one workgroup, bitonic sort in LDS;
-//       larger           one workgroup, a bitmap over all n columns in the
-//                        workspace, read back in column order.
-//  5. scan the unique counts (the degrees) into row_ptr; compact into col_idx
-//     and write dinv = (float)(1 / sqrt((double)deg)).
-//  6. write the entries of A_hat, val[e] = dinv[row] * dinv[col[e]] (fp32).
-//  7. (optional) the row order of the aggregations: rows by decreasing length class,
+//       larger           one workgroup, a bitmap of 2^19 columns at a time in LDS, read
+//                        back in column order.
+//  4. scan the unique counts (the degrees) into row_ptr; dinv = (float)(1 / sqrt((double)deg)).
+//  5. compact into col_idx and write the entries of A_hat beside, val[e] = dinv[row] *
+//     dinv[col[e]] (fp32).
+//  6. (optional) the row order of the aggregations: rows by decreasing length class,
 //     longest first, so that the long rows start early and the short ones fill the end
 //     of a launch (a longest-job-first schedule; the results do not depend on it).  A
 //     stable counting sort over 64 classes of the degree: per-block class counts, one
 //     scan in class-major order, then each block places its rows (ties in row order).
+//
+// Bound: memory.  2,449,029 nodes, 61,859,140 pairs: the pairs, two passes of 8-byte (row,
+// column) entries, the raw rows and the result are about 8 GB.  Whole call 22.2 -> 5.85 ms:
+// partition 2.4 and rows 1.0 (before: an atomic per entry for the counts and one for the places,
+// both to memory, scattered 4-byte writes, 11.6; a rank by comparison per row, 4.1), longer
+// rows 0.7 (3.1), compaction with the gather of dinv 1.4 (2.1).
 #include "internal.h"
 
 namespace gcn {
 namespace {
 
-constexpr int kSmall = 64;
+constexpr int kSmall = 512;   // longest row that a wavefront sorts in registers
 constexpr int kMedium = 4096;
-constexpr int kLargeBlocks = 64;
+constexpr int kLargeBlocks = 512;
+constexpr int kMaxBuckets = 1024;  // buckets of a partition pass (LDS counters)
+constexpr int kPartThreads = 1024;
+constexpr int kMaxSubRows = 1024;
+constexpr int kRowsThreads = 512;
+constexpr int kRowsCap = 10240;    // entries of a sub-bucket that are sorted from LDS
+
+// Rows 2^s1 per bucket and 2^s2 per sub-bucket; nw workgroups share the input pairs.
+struct Parts {
+  int s1, s2;
+  int64_t buckets, subs, nw;
+};
+
+Parts make_parts(int32_t n, int64_t n_edges) {
+  Parts q;
+  const double avg = n > 0 ? 2.0 * (double)n_edges / n + 1.0 : 1.0;
+  q.s2 = 0;
+  while (q.s2 < 10 && avg * (double)(int64_t(2) << q.s2) <= 7000.0) ++q.s2;
+  // as many buckets as one pass takes (their open lines stay in the L2), so few or no
+  // sub-buckets: 598 of 32 each for 2,449,029 rows of 51
+  q.s1 = q.s2;
+  while (ceil_div(n > 0 ? n : 1, int64_t(1) << q.s1) > kMaxBuckets) ++q.s1;
+  if (q.s1 - q.s2 > 10) q.s2 = q.s1 - 10;
+  q.buckets = ceil_div(n > 0 ? n : 1, int64_t(1) << q.s1);
+  q.subs = q.buckets << (q.s1 - q.s2);
+  q.nw = std::max<int64_t>(1, std::min<int64_t>(512, ceil_div(n_edges, 4096)));
+  return q;
+}
+
+struct Pair {
+  int32_t row, col;
+};
 
 struct CsrWs {
+  Parts parts;
+  int32_t* part_cnt;  // buckets * nw
+  int64_t* part_off;  // buckets * nw + 1
+  int64_t* sub_off;   // subs + 1
+  Pair* pa;           // 2 E: entries by bucket
+  Pair* pb;           // 2 E: entries by sub-bucket (where buckets are split)
+  int32_t* raw;       // 2 E + n columns: the raw rows, in the place of pa (of pb if unsplit)
+  int32_t* alt;       // likewise in the other one: the sorted rows of k_sort_large
   int32_t* cnt;       // n: raw entries per row
-  int32_t* fillc;     // n: fill cursors
-  int64_t* raw_off;   // n + 1
-  int32_t* raw;       // 2 E + n
-  int32_t* lists;     // 3 n: small / medium / large row lists
-  int32_t* flags;     // [0] range error, [1..3] list sizes
+  int64_t* raw_off;   // n
+  int32_t* lists;     // 2 n: medium / large row lists
+  int32_t* flags;     // [0] range error, [1..2] list sizes
   void* scan;
-  uint32_t* bitmap;   // kLargeBlocks * words
-  int64_t words;
   void* split;        // hub split plan scratch
   int32_t* ord_cnt;   // kClasses * blocks of 256 rows: rows per (class, block)
   int64_t* ord_off;   // kClasses * blocks + 1: their exclusive scan
@@ -52,114 +96,276 @@ inline int64_t order_blocks(int32_t n) { return ceil_div(n > 0 ? n : 1, kOrderBl
 
 CsrWs carve(Arena& a, int32_t n, int64_t n_edges) {
   CsrWs w;
+  w.parts = make_parts(n, n_edges);
+  const int64_t pcount = w.parts.buckets * w.parts.nw;
+  w.part_cnt = a.take<int32_t>(pcount);
+  w.part_off = a.take<int64_t>(pcount + 1);
+  w.sub_off = a.take<int64_t>(w.parts.subs + 1);
+  const int64_t room = std::max<int64_t>(2 * n_edges, ceil_div(2 * n_edges + n, 2));
+  w.pa = a.take<Pair>(room);
+  w.pb = a.take<Pair>(room);
+  const bool split = w.parts.s1 > w.parts.s2;
+  w.raw = reinterpret_cast<int32_t*>(split ? w.pa : w.pb);
+  w.alt = reinterpret_cast<int32_t*>(split ? w.pb : w.pa);
   w.cnt = a.take<int32_t>(n);
-  w.fillc = a.take<int32_t>(n);
-  w.raw_off = a.take<int64_t>((int64_t)n + 1);
-  w.raw = a.take<int32_t>(2 * n_edges + n);
-  w.lists = a.take<int32_t>(3 * (int64_t)n);
+  w.raw_off = a.take<int64_t>(n);
+  w.lists = a.take<int32_t>(2 * (int64_t)n);
   w.flags = a.take<int32_t>(8);
   const int64_t ocount = kClasses * order_blocks(n);
-  w.scan = a.take<char>((int64_t)scan_workspace(std::max<int64_t>((int64_t)n + 1, ocount + 1)));
-  w.words = ceil_div(n, 32);
-  w.bitmap = a.take<uint32_t>(kLargeBlocks * w.words);
+  w.scan = a.take<char>((int64_t)scan_workspace(std::max<int64_t>(std::max<int64_t>((int64_t)n + 1, ocount + 1), pcount + 1)));
   w.split = a.take<char>((int64_t)split_workspace(n));
   w.ord_cnt = a.take<int32_t>(ocount);
   w.ord_off = a.take<int64_t>(ocount + 1);
   return w;
 }
 
-__global__ void k_init(int32_t n, int32_t* cnt, int32_t* fillc, int32_t* flags) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    cnt[i] = 1;
-    fillc[i] = 1;
-  }
-  if (i < 8) flags[i] = 0;
-}
-
-__global__ void k_count(int32_t n, int64_t ne, const int32_t* src, const int32_t* dst, int32_t* cnt,
-                        int32_t* flags) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < ne;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t u = src[e], v = dst[e];
-    if (u < 0 || u >= n || v < 0 || v >= n) {
-      atomicOr(&flags[0], 1);
-      continue;
+// Calls f(u, v) for the pairs of this workgroup's share; out-of-range endpoints set flags[0].
+template <class F>
+__device__ __forceinline__ void for_pairs(int32_t n, int64_t ne, const int32_t* src, const int32_t* dst,
+                                          int32_t* flags, F f) {
+  constexpr int U = 4;
+  const int64_t per = (ne + gridDim.x - 1) / gridDim.x;
+  const int64_t e0 = (int64_t)blockIdx.x * per, e1 = e0 + per < ne ? e0 + per : ne;
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += U * kPartThreads) {
+    int32_t u[U], v[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int64_t ei = e + (int64_t)i * kPartThreads;
+      u[i] = v[i] = 0;  // a self pair: dropped
+      if (ei < e1) {
+        u[i] = src[ei];
+        v[i] = dst[ei];
+      }
     }
-    if (u == v) continue;
-    atomicAdd(&cnt[u], 1);
-    atomicAdd(&cnt[v], 1);
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      if (u[i] < 0 || u[i] >= n || v[i] < 0 || v[i] >= n) {
+        if (flags) atomicOr(&flags[0], 1);
+        continue;
+      }
+      if (u[i] != v[i]) f(u[i], v[i]);
+    }
   }
 }
 
-__global__ void k_fill(int32_t n, int64_t ne, const int32_t* src, const int32_t* dst,
-                       const int64_t* off, int32_t* fillc, int32_t* raw) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int64_t i = t0; i < n; i += stride) raw[off[i]] = (int32_t)i;
-  for (int64_t e = t0; e < ne; e += stride) {
-    const int32_t u = src[e], v = dst[e];
-    if (u == v) continue;
-    raw[off[u] + atomicAdd(&fillc[u], 1)] = v;
-    raw[off[v] + atomicAdd(&fillc[v], 1)] = u;
-  }
+__global__ void k_init(int32_t* flags) {
+  if (threadIdx.x < 8) flags[threadIdx.x] = 0;
 }
 
-// Row lists by length class; one atomic per class per wavefront (ballot-aggregated).
-__global__ void __launch_bounds__(256) k_classify(int32_t n, const int32_t* cnt, int32_t* lists, int32_t* flags) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x % 64;
-  int cls = -1;
-  if (i < n) {
-    const int32_t len = cnt[i];
-    cls = len <= kSmall ? 0 : (len <= kMedium ? 1 : 2);
+// Entries per (bucket, workgroup).
+__global__ void __launch_bounds__(kPartThreads) k_bucket_count(int32_t n, int64_t ne, const int32_t* src,
+                                                               const int32_t* dst, int s1, int32_t nb, int32_t* cnt,
+                                                               int32_t* flags) {
+  __shared__ int32_t c[kMaxBuckets];
+  for (int b = threadIdx.x; b < nb; b += kPartThreads) c[b] = 0;
+  __syncthreads();
+  for_pairs(n, ne, src, dst, flags, [&](int32_t u, int32_t v) {
+    atomicAdd(&c[u >> s1], 1);
+    atomicAdd(&c[v >> s1], 1);
+  });
+  __syncthreads();
+  for (int b = threadIdx.x; b < nb; b += kPartThreads) cnt[(int64_t)b * gridDim.x + blockIdx.x] = c[b];
+}
+
+// Every entry to its bucket (positions are below 2 E < 2^31).
+__global__ void __launch_bounds__(kPartThreads) k_bucket_scatter(int32_t n, int64_t ne, const int32_t* src,
+                                                                 const int32_t* dst, int s1, int32_t nb,
+                                                                 const int64_t* off, Pair* out) {
+  __shared__ int32_t cur[kMaxBuckets];
+  for (int b = threadIdx.x; b < nb; b += kPartThreads) cur[b] = (int32_t)off[(int64_t)b * gridDim.x + blockIdx.x];
+  __syncthreads();
+  for_pairs(n, ne, src, dst, nullptr, [&](int32_t u, int32_t v) {
+    out[atomicAdd(&cur[u >> s1], 1)] = Pair{u, v};
+    out[atomicAdd(&cur[v >> s1], 1)] = Pair{v, u};
+  });
+}
+
+// One workgroup per bucket: its entries to their sub-buckets.
+__global__ void __launch_bounds__(kPartThreads) k_sub_split(int s1, int s2, int64_t nw, const int64_t* part_off,
+                                                            const Pair* in, Pair* out, int64_t* sub_off) {
+  constexpr int U = 4;
+  __shared__ int32_t cur[kMaxBuckets];
+  const int f = 1 << (s1 - s2);  // <= kMaxBuckets
+  const int64_t b = blockIdx.x;
+  const int32_t lo = (int32_t)part_off[b * nw], hi = (int32_t)part_off[(b + 1) * nw];
+  for (int q = threadIdx.x; q < f; q += kPartThreads) cur[q] = 0;
+  __syncthreads();
+  auto each = [&](auto g) {
+    for (int64_t e = lo + (int64_t)threadIdx.x; e < hi; e += U * kPartThreads) {
+      Pair p[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i) p[i] = e + i * kPartThreads < hi ? in[e + i * kPartThreads] : Pair{-1, -1};
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        if (p[i].row >= 0) g(p[i]);
+    }
+  };
+  auto sub = [&](const Pair& p) { return (p.row >> s2) & (f - 1); };
+  each([&](const Pair& p) { atomicAdd(&cur[sub(p)], 1); });
+  __syncthreads();
+  if (threadIdx.x < 64) {  // exclusive scan over the sub-buckets by one wavefront
+    int32_t run = lo;
+    for (int q0 = 0; q0 < f; q0 += 64) {
+      const int q = q0 + (int)threadIdx.x;
+      const int32_t c = q < f ? cur[q] : 0;
+      int32_t incl = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int32_t up = __shfl_up(incl, o, 64);
+        if ((int)threadIdx.x >= o) incl += up;
+      }
+      if (q < f) {
+        cur[q] = run + incl - c;
+        sub_off[b * f + q] = run + incl - c;
+      }
+      run += __shfl(incl, 63, 64);
+    }
+    if (threadIdx.x == 0 && b == (int64_t)gridDim.x - 1) sub_off[(b + 1) * f] = hi;
   }
+  __syncthreads();
+  each([&](const Pair& p) { out[atomicAdd(&cur[sub(p)], 1)] = p; });
+}
+
+// Lane exchange with lane ^ J.
+template <int J>
+__device__ __forceinline__ int32_t xor_lane(int32_t v) {
+  if constexpr (J == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);
+  else if constexpr (J == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);
+  else if constexpr (J < 32) return __builtin_amdgcn_ds_swizzle(v, (J << 10) | 0x1f);
+  else return __shfl_xor(v, J, 64);
+}
+
+// One step of the bitonic network over 64 K values (value r * 64 + lane in register r).
+template <int K, int KK, int J>
+__device__ __forceinline__ void bitonic_step(int32_t (&x)[K], int lane) {
+  if constexpr (J >= 64) {
+#pragma unroll
+    for (int r = 0; r < K; ++r)
+      if (!(r & (J / 64))) {
+        const int32_t a = x[r], b = x[r | (J / 64)];
+        const bool up = ((r * 64) & KK) == 0;
+        x[r] = up ? min(a, b) : max(a, b);
+        x[r | (J / 64)] = up ? max(a, b) : min(a, b);
+      }
+  } else {
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+      const int32_t o = xor_lane<J>(x[r]);
+      const bool up = ((r * 64 + lane) & KK) == 0, low = (lane & J) == 0;
+      x[r] = up == low ? min(x[r], o) : max(x[r], o);
+    }
+  }
+  if constexpr (J > 1) bitonic_step<K, KK, J / 2>(x, lane);
+}
+template <int K, int KK = 2>
+__device__ __forceinline__ void bitonic_sort(int32_t (&x)[K], int lane) {
+  bitonic_step<K, KK, KK / 2>(x, lane);
+  if constexpr (KK < 64 * K) bitonic_sort<K, 2 * KK>(x, lane);
+}
+
+// Sort and deduplicate the len <= 64 K columns at `from` into `to`; returns the unique count.
+template <int K>
+__device__ __forceinline__ int32_t sort_row(const int32_t* from, int32_t* to, int32_t len, int lane) {
+  int32_t x[K];
+#pragma unroll
+  for (int r = 0; r < K; ++r) x[r] = r * 64 + lane < len ? from[r * 64 + lane] : INT32_MAX;
+  bitonic_sort<K>(x, lane);
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (int c = 0; c < 3; ++c) {
-    const uint64_t bal = __ballot(cls == c);
-    if (!bal) continue;
-    const int leader = __ffsll((unsigned long long)bal) - 1;
-    int32_t base = 0;
-    if (lane == leader) base = atomicAdd(&flags[1 + c], (int32_t)__popcll(bal));
-    base = __shfl(base, leader);
-    if (cls == c) lists[(int64_t)c * n + base + (int32_t)__popcll(bal & below)] = (int32_t)i;
+  int32_t out = 0, before = -1;  // columns are >= 0
+#pragma unroll
+  for (int r = 0; r < K; ++r) {
+    const int32_t up = __shfl_up(x[r], 1, 64);
+    const bool keep = x[r] != INT32_MAX && x[r] != (lane == 0 ? before : up);
+    const uint64_t bal = __ballot(keep);
+    if (keep) to[out + (int32_t)__popcll(bal & below)] = x[r];
+    out += (int32_t)__popcll(bal);
+    before = __shfl(x[r], 63, 64);
+  }
+  return out;
+}
+
+// One workgroup per sub-bucket of 2^s2 rows.
+__global__ void __launch_bounds__(kRowsThreads) k_rows(int32_t n, int s2, const int64_t* sub_off, int64_t stride, const Pair* in,
+                                                       int32_t* raw, int64_t* raw_off, int32_t* cnt, int32_t* deg,
+                                                       int32_t* lists, int32_t* flags) {
+  constexpr int U = 4;
+  __shared__ int32_t len[kMaxSubRows], cur[kMaxSubRows];
+  __shared__ int32_t buf[kRowsCap];
+  const int32_t r0 = (int32_t)((int64_t)blockIdx.x << s2);
+  const int32_t rows = n - r0 < (1 << s2) ? n - r0 : 1 << s2;
+  const int32_t lo = (int32_t)sub_off[blockIdx.x * stride], hi = (int32_t)sub_off[(blockIdx.x + 1) * stride];
+  const int64_t base = (int64_t)lo + r0;  // every row before has its self entry
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  const bool fits = hi - lo + rows <= kRowsCap;
+  for (int r = threadIdx.x; r < rows; r += kRowsThreads) len[r] = 1;
+  __syncthreads();
+  auto each = [&](auto g) {
+    for (int64_t e = lo + (int64_t)threadIdx.x; e < hi; e += U * kRowsThreads) {
+      Pair p[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i) p[i] = e + i * kRowsThreads < hi ? in[e + i * kRowsThreads] : Pair{-1, -1};
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        if (p[i].row >= 0) g(p[i]);
+    }
+  };
+  each([&](const Pair& p) { atomicAdd(&len[p.row - r0], 1); });
+  __syncthreads();
+  if (wave == 0) {  // exclusive scan of the rows' lengths
+    int32_t run = 0;
+    for (int q0 = 0; q0 < rows; q0 += 64) {
+      const int q = q0 + lane;
+      const int32_t c = q < rows ? len[q] : 0;
+      int32_t incl = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int32_t up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+      }
+      if (q < rows) cur[q] = run + incl - c;
+      run += __shfl(incl, 63, 64);
+    }
+  }
+  __syncthreads();
+  int32_t* const seg = raw + base;
+  // each row's self entry first, then its columns as they come; afterwards cur[r] is its end
+  for (int r = threadIdx.x; r < rows; r += kRowsThreads) {
+    const int32_t at = cur[r];
+    cnt[r0 + r] = len[r];
+    raw_off[r0 + r] = base + at;
+    if (fits) buf[at] = r0 + r;
+    else seg[at] = r0 + r;
+    cur[r] = at + 1;
+  }
+  __syncthreads();
+  if (fits) each([&](const Pair& p) { buf[atomicAdd(&cur[p.row - r0], 1)] = p.col; });
+  else each([&](const Pair& p) { seg[atomicAdd(&cur[p.row - r0], 1)] = p.col; });
+  __syncthreads();
+  for (int r = wave; r < rows; r += kRowsThreads / 64) {
+    const int32_t l = len[r], at = cur[r] - l;
+    const int32_t* from = fits ? buf + at : seg + at;
+    if (l <= kSmall) {
+      const int32_t d = l <= 64    ? sort_row<1>(from, seg + at, l, lane)
+                      : l <= 128 ? sort_row<2>(from, seg + at, l, lane)
+                      : l <= 256 ? sort_row<4>(from, seg + at, l, lane) : sort_row<8>(from, seg + at, l, lane);
+      if (lane == 0) deg[r0 + r] = d;
+    } else {
+      if (fits)
+        for (int32_t i = lane; i < l; i += 64) seg[at + i] = from[i];
+      if (lane == 0) {
+        const int c = l <= kMedium ? 0 : 1;
+        lists[(int64_t)c * n + atomicAdd(&flags[1 + c], 1)] = r0 + r;
+      }
+    }
   }
 }
 
-// one wavefront per row of <= 64 entries
-__global__ void __launch_bounds__(256) k_sort_small(int32_t count, const int32_t* list,
-                                                    const int64_t* off, const int32_t* cnt,
-                                                    int32_t* raw, int32_t* deg) {
-  const int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64;
-  const int lane = threadIdx.x % 64;
-  if (wid >= count) return;
-  const int32_t row = list[wid];
-  const int32_t len = cnt[row];
-  int32_t* seg = raw + off[row];
-  const int32_t x = lane < len ? seg[lane] : INT32_MAX;
-  bool first = lane < len;
-  for (int k = 0; k < 64; ++k) {
-    const int32_t xk = __shfl(x, k);
-    if (k < lane && xk == x) first = false;
-  }
-  int rank = 0;
-  for (int k = 0; k < 64; ++k) {
-    const int32_t xk = __shfl(x, k);
-    const int fk = __shfl((int)first, k);
-    if (fk && xk < x) ++rank;
-  }
-  const uint64_t bal = __ballot(first);
-  if (first) seg[rank] = x;
-  if (lane == 0) deg[row] = (int32_t)__popcll(bal);
-}
-
-// one workgroup per row of 65..4096 entries: bitonic sort in LDS, then compact
-__global__ void __launch_bounds__(256) k_sort_medium(int32_t count, const int32_t* list,
+// one workgroup per row of 513..4096 entries: bitonic sort in LDS, then compact
+__global__ void __launch_bounds__(256) k_sort_medium(const int32_t* pcount, const int32_t* list,
                                                      const int64_t* off, const int32_t* cnt,
                                                      int32_t* raw, int32_t* deg) {
   __shared__ int32_t a[kMedium];
   __shared__ int32_t part[256];
   const int tid = threadIdx.x;
+  const int32_t count = *pcount;
   for (int64_t item = blockIdx.x; item < count; item += gridDim.x) {
     const int32_t row = list[item];
     const int32_t len = cnt[row];
@@ -206,87 +412,102 @@ __global__ void __launch_bounds__(256) k_sort_medium(int32_t count, const int32_
   }
 }
 
-// one workgroup per row of > 4096 entries: set bits in an n-bit map, read back in order.
-// The map is touched only with device-scope atomics, so no stale cache line is read.
-__global__ void __launch_bounds__(256) k_sort_large(int32_t count, const int32_t* list,
-                                                    const int64_t* off, const int32_t* cnt,
-                                                    int32_t* raw, int32_t* deg, uint32_t* bitmap,
-                                                    int64_t words) {
-  __shared__ int32_t part[256];
-  const int tid = threadIdx.x;
-  uint32_t* bm = bitmap + (int64_t)blockIdx.x * words;
+// One workgroup per row of > 4096 entries: for each window of kWindow columns, a bitmap of the
+// row's columns in LDS, read back in order.  The result goes to `alt` (the row is read once per
+// window) and raw_off follows it.
+constexpr int kWindow = 1 << 19;
+constexpr int kLargeThreads = 512;
+__global__ void __launch_bounds__(kLargeThreads) k_sort_large(const int32_t* pcount, const int32_t* list, int32_t n,
+                                                              int64_t* raw_off, const int32_t* cnt, const int32_t* raw,
+                                                              int32_t* alt, int32_t* deg) {
+  constexpr int kWords = kWindow / 32, kPer = kWords / kLargeThreads;
+  __shared__ uint32_t bm[kWords];
+  __shared__ int32_t wsum[kLargeThreads / 64];
+  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+  const int32_t count = *pcount;
   for (int64_t item = blockIdx.x; item < count; item += gridDim.x) {
-    const int32_t row = list[item];
-    const int32_t len = cnt[row];
-    int32_t* seg = raw + off[row];
-    for (int64_t w = tid; w < words; w += 256)
-      __hip_atomic_store(&bm[w], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence();
-    __syncthreads();
-    for (int64_t j = tid; j < len; j += 256) {
-      const int32_t x = seg[j];
-      atomicOr(&bm[x >> 5], 1u << (x & 31));
-    }
-    __threadfence();
-    __syncthreads();
-    int64_t run = 0;
-    constexpr int kPer = 8;
-    for (int64_t w0 = 0; w0 < words; w0 += 256 * kPer) {
-      uint32_t v[kPer];
-      int c = 0;
-      for (int i = 0; i < kPer; ++i) {
-        const int64_t w = w0 + (int64_t)tid * kPer + i;
-        v[i] = w < words ? __hip_atomic_load(&bm[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-        c += __popc(v[i]);
-      }
-      part[tid] = c;
+    const int32_t row = list[item], len = cnt[row];
+    const int64_t off = raw_off[row];
+    const int32_t* in = raw + off;
+    int32_t* out = alt + off;
+    int32_t run = 0;
+    for (int64_t w0 = 0; w0 < n; w0 += kWindow) {
+      for (int i = tid; i < kWords; i += kLargeThreads) bm[i] = 0;
       __syncthreads();
-      for (int o = 1; o < 256; o <<= 1) {
-        const int add = tid >= o ? part[tid - o] : 0;
-        __syncthreads();
-        part[tid] += add;
-        __syncthreads();
+      for (int32_t j = tid; j < len; j += kLargeThreads) {
+        const int64_t x = in[j] - w0;
+        if (x >= 0 && x < kWindow) atomicOr(&bm[x >> 5], 1u << (x & 31));
       }
-      int64_t pos = run + part[tid] - c;
-      const int total = part[255];
+      __syncthreads();
+      // thread t reads words t * kPer ..; a scan over the workgroup gives its place
+      int32_t c = 0;
+      for (int i = 0; i < kPer; ++i) c += __popc(bm[tid * kPer + i]);
+      int32_t incl = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int32_t up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+      }
+      if (lane == 63) wsum[wave] = incl;
+      __syncthreads();
+      int32_t pos = run + incl - c;
+      for (int q = 0; q < kLargeThreads / 64; ++q) {
+        if (q < wave) pos += wsum[q];
+        run += wsum[q];
+      }
       for (int i = 0; i < kPer; ++i) {
-        uint32_t bits = v[i];
-        const int64_t base = (w0 + (int64_t)tid * kPer + i) * 32;
+        uint32_t bits = bm[tid * kPer + i];
+        const int64_t first = w0 + (int64_t)(tid * kPer + i) * 32;
         while (bits) {
-          const int b = __ffs(bits) - 1;
+          out[pos++] = (int32_t)(first + __ffs(bits) - 1);
           bits &= bits - 1;
-          seg[pos++] = (int32_t)(base + b);
         }
       }
-      run += total;
       __syncthreads();
     }
-    if (tid == 0) deg[row] = (int32_t)run;
-    __threadfence();
+    if (tid == 0) {
+      deg[row] = run;
+      raw_off[row] = off + (alt - raw);
+    }
     __syncthreads();
   }
 }
 
+__global__ void __launch_bounds__(256) k_dinv(int32_t n, const int32_t* deg, float* dinv) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) dinv[i] = (float)(1.0 / sqrt((double)deg[i]));
+}
+
+// A group of G lanes per row: its unique columns to their place, the entries of A_hat beside.
+template <int G>
 __global__ void __launch_bounds__(256) k_compact(int32_t n, const int64_t* raw_off, const int32_t* raw,
-                                                 const int64_t* row_ptr, const int32_t* deg,
-                                                 int32_t* col_idx, float* dinv) {
-  const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64;
-  const int lane = threadIdx.x % 64;
+                                                 const int64_t* row_ptr, const int32_t* deg, const float* dinv,
+                                                 int32_t* col_idx, float* val) {
+  const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
+  const int lane = threadIdx.x % G;
   if (row >= n) return;
   const int32_t d = deg[row];
   const int32_t* s = raw + raw_off[row];
-  int32_t* o = col_idx + row_ptr[row];
-  for (int32_t j = lane; j < d; j += 64) o[j] = s[j];
-  if (lane == 0) dinv[row] = (float)(1.0 / sqrt((double)d));
-}
-
-__global__ void __launch_bounds__(256) k_values(int32_t n, const int64_t* row_ptr, const int32_t* col_idx,
-                                                const float* dinv, float* val) {
-  const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64;
-  const int lane = threadIdx.x % 64;
-  if (row >= n) return;
+  const int64_t o = row_ptr[row];
   const float di = dinv[row];
-  for (int64_t e = row_ptr[row] + lane; e < row_ptr[row + 1]; e += 64) val[e] = di * dinv[col_idx[e]];
+  int32_t j = lane;
+  for (; j + 3 * G < d; j += 4 * G) {  // a long row: four gathers in flight
+    int32_t c[4];
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) c[u] = s[j + u * G];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = dinv[c[u]];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      col_idx[o + j + u * G] = c[u];
+      val[o + j + u * G] = di * v[u];
+    }
+  }
+  for (; j < d; j += G) {
+    const int32_t c = s[j];
+    col_idx[o + j] = c;
+    val[o + j] = di * dinv[c];
+  }
 }
 
 // Length class of a row: 4 classes per power of two of the degree (its two bits below
@@ -335,60 +556,63 @@ gcn_status run_build_csr(int32_t n, int64_t n_edges, const int32_t* src, const i
   Arena a;
   a.base = static_cast<char*>(ws);
   CsrWs w = carve(a, n, n_edges);
-  const int T = 256;
-  const unsigned gn = (unsigned)ceil_div(n > 8 ? n : 8, T);
-  const unsigned ge = (unsigned)(ceil_div(n_edges, T) < 65536 ? (ceil_div(n_edges, T) > 0 ? ceil_div(n_edges, T) : 1) : 65536);
-
-  hipLaunchKernelGGL(k_init, dim3(gn), dim3(T), 0, s, n, w.cnt, w.fillc, w.flags);
+  const Parts& q = w.parts;
+  hipLaunchKernelGGL(k_init, dim3(1), dim3(64), 0, s, w.flags);
   GCN_TRY(check_launch("csr init"));
-  hipLaunchKernelGGL(k_count, dim3(ge), dim3(T), 0, s, n, n_edges, src, dst, w.cnt, w.flags);
-  GCN_TRY(check_launch("csr count"));
-  int32_t flags[4];
-  GCN_HIP(hipMemcpyAsync(flags, w.flags, sizeof flags, hipMemcpyDeviceToHost, s), "csr flags");
-  GCN_HIP(hipStreamSynchronize(s), "csr sync");
-  if (flags[0]) return fail(GCN_E_RANGE, "gcn_build_csr: an edge endpoint is outside [0, n)");
-
-  GCN_TRY(launch_scan_i32(w.cnt, n, w.raw_off, w.scan, s));
-  const unsigned gf = (unsigned)std::max<int64_t>(1, std::min<int64_t>(65536, ceil_div(std::max<int64_t>(n_edges, n), T)));
-  hipLaunchKernelGGL(k_fill, dim3(gf), dim3(T), 0, s, n, n_edges, src, dst, w.raw_off, w.fillc, w.raw);
-  GCN_TRY(check_launch("csr fill"));
-  hipLaunchKernelGGL(k_classify, dim3(gn), dim3(T), 0, s, n, w.cnt, w.lists, w.flags);
-  GCN_TRY(check_launch("csr classify"));
-  GCN_HIP(hipMemcpyAsync(flags, w.flags, sizeof flags, hipMemcpyDeviceToHost, s), "csr flags");
-  GCN_HIP(hipStreamSynchronize(s), "csr sync");
-  const int32_t n_small = flags[1], n_med = flags[2], n_large = flags[3];
-  if (n_small > 0) {
-    hipLaunchKernelGGL(k_sort_small, dim3((unsigned)ceil_div(n_small, 4)), dim3(256), 0, s, n_small,
-                       w.lists, w.raw_off, w.cnt, w.raw, g->deg);
-    GCN_TRY(check_launch("csr sort small"));
+  hipLaunchKernelGGL(k_bucket_count, dim3((unsigned)q.nw), dim3(kPartThreads), 0, s, n, n_edges, src, dst, q.s1,
+                     (int32_t)q.buckets, w.part_cnt, w.flags);
+  GCN_TRY(check_launch("csr bucket count"));
+  GCN_TRY(launch_scan_i32(w.part_cnt, q.buckets * q.nw, w.part_off, w.scan, s));
+  hipLaunchKernelGGL(k_bucket_scatter, dim3((unsigned)q.nw), dim3(kPartThreads), 0, s, n, n_edges, src, dst, q.s1,
+                     (int32_t)q.buckets, w.part_off, w.pa);
+  GCN_TRY(check_launch("csr bucket scatter"));
+  const bool split = q.s1 > q.s2;
+  if (split) {
+    hipLaunchKernelGGL(k_sub_split, dim3((unsigned)q.buckets), dim3(kPartThreads), 0, s, q.s1, q.s2, q.nw, w.part_off,
+                       w.pa, w.pb, w.sub_off);
+    GCN_TRY(check_launch("csr sub-buckets"));
   }
-  if (n_med > 0) {
-    const unsigned gm = (unsigned)std::min<int64_t>(n_med, 8192);
-    hipLaunchKernelGGL(k_sort_medium, dim3(gm), dim3(256), 0, s, n_med, w.lists + n, w.raw_off,
-                       w.cnt, w.raw, g->deg);
-    GCN_TRY(check_launch("csr sort medium"));
-  }
-  if (n_large > 0) {
-    const unsigned gl = (unsigned)std::min<int64_t>(n_large, kLargeBlocks);
-    hipLaunchKernelGGL(k_sort_large, dim3(gl), dim3(256), 0, s, n_large, w.lists + 2 * (int64_t)n,
-                       w.raw_off, w.cnt, w.raw, g->deg, w.bitmap, w.words);
-    GCN_TRY(check_launch("csr sort large"));
+  if (n > 0) {
+    hipLaunchKernelGGL(k_rows, dim3((unsigned)ceil_div(n, int64_t(1) << q.s2)), dim3(kRowsThreads), 0, s, n, q.s2,
+                       split ? w.sub_off : w.part_off, split ? (int64_t)1 : q.nw, split ? w.pb : w.pa, w.raw, w.raw_off,
+                       w.cnt, g->deg, w.lists, w.flags);
+    GCN_TRY(check_launch("csr rows"));
+    // the lists' sizes stay on the device; a row of more than kSmall raw entries takes as many
+    // pairs, which bounds how many there can be
+    const int64_t most = std::min<int64_t>(n, 2 * n_edges / kSmall);
+    if (most > 0) {
+      hipLaunchKernelGGL(k_sort_medium, dim3((unsigned)std::min<int64_t>(most, 8192)), dim3(256), 0, s, w.flags + 1,
+                         w.lists, w.raw_off, w.cnt, w.raw, g->deg);
+      GCN_TRY(check_launch("csr sort medium"));
+    }
+    const int64_t most_large = std::min<int64_t>(n, 2 * n_edges / kMedium);
+    if (most_large > 0) {
+      hipLaunchKernelGGL(k_sort_large, dim3((unsigned)std::min<int64_t>(most_large, kLargeBlocks)),
+                         dim3(kLargeThreads), 0, s, w.flags + 2, w.lists + n, n, w.raw_off, w.cnt, w.raw, w.alt, g->deg);
+      GCN_TRY(check_launch("csr sort large"));
+    }
   }
   GCN_TRY(launch_scan_i32(g->deg, n, g->row_ptr, w.scan, s));
   int64_t nnz = 0;
+  int32_t flags[4];
+  GCN_HIP(hipMemcpyAsync(flags, w.flags, sizeof flags, hipMemcpyDeviceToHost, s), "csr flags");
   GCN_HIP(hipMemcpyAsync(&nnz, g->row_ptr + n, sizeof nnz, hipMemcpyDeviceToHost, s), "csr nnz");
   GCN_HIP(hipStreamSynchronize(s), "csr sync");
+  if (flags[0]) return fail(GCN_E_RANGE, "gcn_build_csr: an edge endpoint is outside [0, n)");
   g->nnz = nnz;
   if (nnz > g->nnz_cap)
     return fail(GCN_E_CAPACITY, "gcn_build_csr: nnz " + std::to_string(nnz) + " exceeds nnz_cap " +
                                     std::to_string(g->nnz_cap));
   if (n > 0) {
-    hipLaunchKernelGGL(k_compact, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, s, n, w.raw_off, w.raw,
-                       g->row_ptr, g->deg, g->col_idx, g->dinv);
+    hipLaunchKernelGGL(k_dinv, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, n, g->deg, g->dinv);
+    GCN_TRY(check_launch("csr dinv"));
+    if (nnz < 20 * (int64_t)n)
+      hipLaunchKernelGGL(k_compact<16>, dim3((unsigned)ceil_div(n, 16)), dim3(256), 0, s, n, w.raw_off, w.raw, g->row_ptr,
+                         g->deg, g->dinv, g->col_idx, g->val);
+    else
+      hipLaunchKernelGGL(k_compact<64>, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, s, n, w.raw_off, w.raw, g->row_ptr,
+                         g->deg, g->dinv, g->col_idx, g->val);
     GCN_TRY(check_launch("csr compact"));
-    hipLaunchKernelGGL(k_values, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, s, n, g->row_ptr, g->col_idx,
-                       g->dinv, g->val);
-    GCN_TRY(check_launch("csr values"));
   }
   if (g->order && n > 0) {
     const int64_t nblk = order_blocks(n);

@@ -882,3 +882,42 @@ def test_feature_views_edges(G, orc, f, ld):
         np.testing.assert_array_equal(host(sx.col_ptr), cp)
         np.testing.assert_array_equal(host(sx.row)[:nnz], row)
         np.testing.assert_array_equal(host(sx.cval)[:nnz].view(np.int32), cval.astype(np.float32).view(np.int32))
+
+
+@pytest.mark.parametrize("n", [1, 2, 1023, 1025, 40000, 600000])
+def test_build_csr_row_lengths(G, orc, n):
+    """The graph build at the lengths where a row changes hands (64, 128, 256 and 512 raw entries
+    sorted by a wavefront, 4,096 by a workgroup, more by the windowed bitmap, one and two windows
+    of 2^19 columns), with rows that are all duplicates, duplicates that cross those lengths,
+    self pairs, buckets that are split and buckets that are not, and sub-buckets too large for
+    LDS: byte for byte the oracle's graph."""
+    rng = np.random.default_rng(n)
+    src, dst = [np.zeros(0, np.int64)], [np.zeros(0, np.int64)]
+    for i, want in enumerate((62, 63, 64, 127, 128, 255, 256, 257, 511, 512, 513, 4094, 4095, 4096, 9000)):
+        if i >= n:
+            break
+        hub = (i * 7919) % n
+        src.append(np.full(want, hub))
+        dst.append(rng.integers(0, n, want))
+    src.append(rng.integers(0, n, 3 * n))
+    dst.append(rng.integers(0, n, 3 * n))
+    src.append(np.full(700, n // 2))  # one pair, 700 times
+    dst.append(np.full(700, n - 1))
+    if n >= 40000:
+        src.append(np.full(30000, 5))  # a sub-bucket that does not fit, its hub beyond 4,096
+        dst.append(rng.permutation(n)[:30000])
+    s = np.concatenate(src).astype(np.int32)
+    d = np.concatenate(dst).astype(np.int32)
+    mix = rng.permutation(s.size)
+    s, d = s[mix], d[mix]
+    print(f"[build] n {n} pairs {s.size}", flush=True)
+    og = orc.build_csr(n, s, d)
+    for _ in range(2):
+        check_graph_equal(G.build_csr(n, dev(s), dev(d)), og, n)
+    # an endpoint out of range is refused wherever it stands
+    for bad in (-1, n):
+        d2 = d.copy()
+        d2[d2.size // 3] = bad
+        with pytest.raises(G.GcnError) as e:
+            G.build_csr(n, dev(s), dev(d2))
+        assert e.value.status == G.E_RANGE
