@@ -1,4 +1,4 @@
-// agg_blocked.hip -- the aggregation with 16-byte rows wider than 16 columns.
+// agg_blocked.hip -- the aggregation with 16-byte rows.
 //
 // Z[u,:] = sum_{e in row u} val[e] * M[col[e], :]  (+ bias, epilogue), as in aggregate.hip, for
 // matrices M below 4 GB: a wavefront sums one row at a time over a panel of 4 LANES columns.
@@ -13,7 +13,8 @@
 //
 // Long rows: a piece of more than kHub entries is cut over the four wavefronts of its
 // workgroup; rows beyond GCN_SPLIT_MIN with a split plan are summed chunk by chunk by
-// wavefronts that start ahead of the others in the same launch.
+// wavefronts that start ahead of the others in the same launch.  (On graphs of few rows the
+// longest one bounds the call: 2,500 entries walked by one lane group took 110 us.)
 //
 // Dense graphs are blocked by source rows.  Gathered in row order, M is read from behind the L2
 // once per entry (4 nnz w bytes).  Where a row has enough entries in each block of M's rows
@@ -27,24 +28,10 @@
 // 7,390, width 41 3,050 -> 1,930; 169,343 rows of 15, width 256 342 -> 306, 128 170 -> 157, 40
 // 106 -> 76; RMAT 2^21 rows of 31, width 128 4,000 -> 3,610; 2,449,029 rows of 51, width 256
 // 17,900 -> 17,600 (bound by the fabric); 100,000 rows of 32, width 128 272 -> 171.
-#include "agg_device.h"
-
-#include <cstdlib>
+#include "agg_walk.h"
 
 namespace gcn {
 namespace {
-
-constexpr int kBlockThreads = 256;
-
-// A wavefront holds SL = 64 / LANES slices of LANES lanes and sums one row's piece at a time,
-// in chunks of up to 64 entries cut into SL runs; lane i of a slice requests the i-th entry of
-// its run, so that step u takes the entry of lane u of each slice: one LDS-crossbar swizzle
-// with a constant pattern, no index arithmetic per gather.
-template <int LANES, int U>
-__device__ __forceinline__ uint32_t from_lane(uint32_t v) {
-  constexpr int pattern = (U << 5) | (0x1f & ~(LANES - 1));  // and-mask keeps the slice, or-mask names lane U
-  return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, pattern);
-}
 
 // Gathers of steps U .. U + N - 1.  FULL: every slice has an entry in each; else step u is this
 // slice's only if u < mine (a skipped entry must not be multiplied by zero instead: the row
@@ -75,37 +62,32 @@ __device__ __forceinline__ void gather_add(float w, const float4* x, float4& acc
   (std::make_integer_sequence<int, N>{});
 }
 
-// Steps U .. U + 7 of a chunk whose slices hold `mine` entries, between `least` and `most`
-// (uniform), half of them at a time where the chunk ends among them; `between` runs after the
-// loads are issued.
+// Steps U .. U + 7 of a chunk, half of them at a time where the chunk ends among them (slices of
+// 4 lanes have four steps in all); `between` runs after the loads are issued.
 template <int LANES, int U, class Between>
-__device__ __forceinline__ void gather_eight(const char* Mc, uint32_t off, float w, uint32_t lane_off, int mine,
-                                             int least, int most, float4& acc, Between between) {
+__device__ __forceinline__ void gather_eight(const char* Mc, uint32_t off, float w, uint32_t lane_off, const Runs& rn,
+                                             float4& acc, Between between) {
   float4 x[8];
-  if (least >= U + 8) {
-    gather_load<LANES, U, 8, true>(Mc, off, lane_off, mine, x);
-    between();
-    gather_add<LANES, U, 8>(w, x, acc);
-  } else if (most > U + 4) {
-    if (least >= U + 4) gather_load<LANES, U, 4, true>(Mc, off, lane_off, mine, x);
-    else gather_load<LANES, U, 4, false>(Mc, off, lane_off, mine, x);
-    gather_load<LANES, U + 4, 4, false>(Mc, off, lane_off, mine, x + 4);
-    between();
-    gather_add<LANES, U, 8>(w, x, acc);
-  } else {
-    gather_load<LANES, U, 4, false>(Mc, off, lane_off, mine, x);
-    between();
-    gather_add<LANES, U, 4>(w, x, acc);
+  if constexpr (LANES >= 8) {
+    if (rn.least >= U + 8) {
+      gather_load<LANES, U, 8, true>(Mc, off, lane_off, rn.have, x);
+      between();
+      gather_add<LANES, U, 8>(w, x, acc);
+      return;
+    }
+    if (rn.run > U + 4) {
+      if (rn.least >= U + 4) gather_load<LANES, U, 4, true>(Mc, off, lane_off, rn.have, x);
+      else gather_load<LANES, U, 4, false>(Mc, off, lane_off, rn.have, x);
+      gather_load<LANES, U + 4, 4, false>(Mc, off, lane_off, rn.have, x + 4);
+      between();
+      gather_add<LANES, U, 8>(w, x, acc);
+      return;
+    }
   }
+  gather_load<LANES, U, 4, false>(Mc, off, lane_off, rn.have, x);
+  between();
+  gather_add<LANES, U, 4>(w, x, acc);
 }
-
-// The entries of one row whose source rows lie in one block.
-struct __attribute__((aligned(16))) Piece {
-  int64_t beg;
-  int32_t len, row;
-};
-
-constexpr int kWavesPerBlock = kBlockThreads / 64;
 
 // Rows longer than GCN_SPLIT_MIN (one block only): `groups` workgroups ahead of the others sum
 // one chunk of such a row per wavefront into part (pitch pw); k_finish_long adds a row's chunks.
@@ -115,9 +97,6 @@ struct LongRows {
   int64_t pw;
   int32_t groups;
 };
-constexpr int kMaxRounds = 64 / kWavesPerBlock / kWavesPerBlock;  // one lane per item at most
-constexpr int kHub = 512;  // eight chunks: about 10 us for one wavefront
-
 // The finished columns of one row (every slice holds them; slice 0 writes): ReLU with its
 // bitmask, or the mask (mk, this lane's columns of it).
 template <int LANES, int EPI>
@@ -135,7 +114,7 @@ __device__ __forceinline__ void store_row(const AggParams& p, int64_t row, float
         bits |= c0 + 2 < p.w && v.z > 0.f ? 4u : 0u;
         bits |= c0 + 3 < p.w && v.w > 0.f ? 8u : 0u;
       }
-      bits = group_or<8>(bits << (c0 % 32));
+      bits = group_or<(LANES < 8 ? LANES : 8)>(bits << (c0 % 32));
       if (L.slot == 0 && cok && L.lane % 8 == 0) p.relu_bits[row * p.ld_relu_bits + c0 / 32] = bits;
     }
     v = make_float4(fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f));
@@ -160,21 +139,13 @@ __device__ __forceinline__ void store_row(const AggParams& p, int64_t row, float
 }
 
 // Workgroup b's wavefront w sums the pieces of rows 4 b + w, 4 b + w + nwaves, ... (`rounds` of
-// them; in processing order when blocked, so that rows of like length run together).  A piece
-// of more than kHub entries is shared: each of the four wavefronts of its workgroup sums a
-// quarter, and the quarters meet in LDS.  Which pieces are shared depends on the piece alone, so
-// the results do not depend on the order.
+// them; in processing order when blocked, so that rows of like length run together).
 template <int LANES, int EPI>
-__global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, const Piece* pieces, int32_t block,
+__global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const Piece* pieces, int32_t block,
                                                                int32_t nblock, int32_t rounds, LongRows lr) {
   constexpr int SL = 64 / LANES;
-  __shared__ __attribute__((aligned(16))) float s_part[2][kWavesPerBlock][4 * LANES];
-  Lanes L;
-  L.gw = 64;
-  L.lig = threadIdx.x & 63;
-  L.slot = L.lig / LANES;
-  L.lane = L.lig & (LANES - 1);
-  L.c0 = ((int)blockIdx.y * LANES + L.lane) * 4;
+  __shared__ __attribute__((aligned(16))) float s_part[2][kWalkWaves][4 * LANES];
+  const Lanes L = walk_lanes<LANES>();
   const bool cok = L.c0 < p.w;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const char* Mc = reinterpret_cast<const char*>(p.M);
@@ -184,13 +155,13 @@ __global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, cons
 
   // Lane 4 r + q holds the piece of round r, wavefront q: every wavefront knows all of them.
   const bool chunks = (int)blockIdx.x < lr.groups;
-  const int64_t nwaves = (int64_t)((int)gridDim.x - lr.groups) * kWavesPerBlock;
-  const int64_t hi = (int64_t)((int)blockIdx.x - (chunks ? 0 : lr.groups)) * kWavesPerBlock + L.lig % kWavesPerBlock +
-                     (int64_t)(L.lig / kWavesPerBlock) * nwaves;
+  const int64_t nwaves = (int64_t)((int)gridDim.x - lr.groups) * kWalkWaves;
+  const int64_t hi = (int64_t)((int)blockIdx.x - (chunks ? 0 : lr.groups)) * kWalkWaves + L.lig % kWalkWaves +
+                     (int64_t)(L.lig / kWalkWaves) * nwaves;
   Piece h{0, 0, -1};
   if (chunks) {
     rounds = 1;
-    if (L.lig < kWavesPerBlock && hi < lr.sp.n_chunk) {
+    if (L.lig < kWalkWaves && hi < lr.sp.n_chunk) {
       const int64_t ch = lr.sp.order ? lr.sp.order[hi] : hi;
       const int32_t o = lr.sp.owner[ch], row = lr.sp.rows[o];
       h.beg = p.row_ptr[row] + (ch - lr.sp.first[o]) * (int64_t)GCN_SPLIT_CHUNK;
@@ -198,7 +169,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, cons
       h.len = (int)(left < GCN_SPLIT_CHUNK ? left : GCN_SPLIT_CHUNK);
       h.row = (int)ch;
     }
-  } else if (L.lig < kWavesPerBlock * rounds && hi < p.n) {
+  } else if (L.lig < kWalkWaves * rounds && hi < p.n) {
     if (nblock > 1) {
       h = pieces[(int64_t)block * p.n + hi];
     } else {
@@ -206,35 +177,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, cons
       if (lr.groups == 0 || end - beg <= GCN_SPLIT_MIN) h = Piece{beg, (int32_t)(end - beg), (int32_t)hi};
     }
   }
-  const uint64_t hubs = chunks ? 0 : __ballot(h.len > kHub);
-  // Lane t then takes this wavefront's item t: its own piece of a round, or its quarter of a
-  // shared one (kind: the wavefront that finishes it, or -1).  Every wavefront has the shared
-  // items in the same order, with one barrier each.
-  int nitems = rounds, src = kWavesPerBlock * L.lig + wave, kind = -1;
-  if (hubs) {
-    nitems = 0;
-    src = 0;
-    for (int r = 0; r < rounds; ++r) {
-      const uint32_t shared = (uint32_t)(hubs >> (kWavesPerBlock * r)) & ((1u << kWavesPerBlock) - 1);
-      for (int q = 0; q < kWavesPerBlock; ++q) {
-        if (!((shared >> q) & 1) && q != wave) continue;
-        if (L.lig == nitems) {
-          src = kWavesPerBlock * r + q;
-          kind = (shared >> q) & 1 ? q : -1;
-        }
-        ++nitems;
-      }
-    }
-  }
-  const int h_row = __shfl(h.row, src, 64);
-  int h_len = __shfl(h.len, src, 64);
-  int64_t h_beg = __shfl(h.beg, src, 64);
-  if (kind >= 0) {
-    const int part = (h_len + kWavesPerBlock - 1) / kWavesPerBlock;
-    const int lo = part * wave < h_len ? part * wave : h_len;
-    h_beg += lo;
-    h_len = h_len - lo < part ? h_len - lo : part;
-  }
+  const Items items = make_items(h, rounds, wave, L.lig, !chunks);
 
   // Epilogue inputs that need no waiting for at a row's end: the bias of this lane's columns,
   // the mean's factor of the item's row.
@@ -245,31 +188,18 @@ __global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, cons
     if (L.c0 + 2 < p.w) bias.z = p.bias[L.c0 + 2];
     if (L.c0 + 3 < p.w) bias.w = p.bias[L.c0 + 3];
   }
-  const float h_scale = EPI != AGG_SOFTMAX && last && !chunks && h_row >= 0 ? row_scale(p, h_row) : 1.f;
+  const float h_scale = EPI != AGG_SOFTMAX && last && !chunks && items.row >= 0 ? row_scale(p, items.row) : 1.f;
 
   // The entries are requested two chunks ahead of the gathers: a chunk's indices come from
-  // behind the L2, its gathers mostly from it.  Every item has at least one (empty) chunk.
-  int f_item = 0, f_done = 0;
+  // behind the L2, its gathers mostly from it.
+  Cursor<LANES> cursor;
   auto fetch = [&](int& j, float& w) __attribute__((always_inline)) {
     j = 0;
     w = 0.f;
-    if (f_item >= nitems) return;
-    const int f_len = __builtin_amdgcn_readlane(h_len, f_item);
-    const uint32_t blo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)h_beg, f_item);
-    const uint32_t bhi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)h_beg >> 32), f_item);
-    const int64_t base = (int64_t)(((uint64_t)bhi << 32) | blo) + f_done;
-    // the chunk's entries in SL runs, one per slice
-    const int cnt = f_len - f_done < 64 ? f_len - f_done : 64;
-    const int run = (cnt + SL - 1) / SL;
-    const int at = L.slot * run + L.lane;
-    if (L.lane < run && at < cnt) {
-      j = p.col[base + at];
-      if (p.kind == AGG_W_VAL) w = p.val[base + at];
-    }
-    f_done += 64;
-    if (f_done >= f_len) {
-      ++f_item;
-      f_done = 0;
+    int64_t at;
+    if (cursor.next(items, L, &at)) {
+      j = p.col[at];
+      if (p.kind == AGG_W_VAL) w = p.val[at];
     }
   };
   int j0, j1;
@@ -287,10 +217,10 @@ __global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, cons
     kept = 0;
   };
   int parity = 0;
-  for (int t = 0; t < nitems; ++t) {
-    const int row = __builtin_amdgcn_readlane(h_row, t);
-    const int len = __builtin_amdgcn_readlane(h_len, t);
-    const int fin = __builtin_amdgcn_readlane(kind, t);
+  for (int t = 0; t < items.n; ++t) {
+    const int row = __builtin_amdgcn_readlane(items.row, t);
+    const int len = __builtin_amdgcn_readlane(items.len, t);
+    const int fin = __builtin_amdgcn_readlane(items.kind, t);
     const bool mine = row >= 0 && (fin < 0 || fin == wave);
     float* z = (chunks ? lr.part + row * lr.pw : p.Z + (int64_t)(row < 0 ? 0 : row) * p.ldz) + L.c0;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -301,23 +231,20 @@ __global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, cons
     int done = 0;
     do {
       const int cnt = len - done < 64 ? len - done : 64;
-      const int run = (cnt + SL - 1) / SL;
-      const int left = cnt - L.slot * run;
-      const int have = left < run ? left : run;
-      const int tail = cnt - (SL - 1) * run, least = tail < 0 ? 0 : tail;
+      const Runs rn = runs_of<LANES>(cnt, L.slot);
       const uint32_t off = (uint32_t)j0 * pitch;
       float w = w0;
       if (p.kind != AGG_W_VAL)
-        w = L.lane < have ? (p.kind == AGG_W_COLMEAN ? 1.f / (float)p.deg[j0] : 1.f) : 0.f;
+        w = L.lane < rn.have ? (p.kind == AGG_W_COLMEAN ? 1.f / (float)p.deg[j0] : 1.f) : 0.f;
       j0 = j1;
       w0 = w1;
-      gather_eight<LANES, 0>(Mc, off, w, lane_off, have, least, run, acc,
-                             [&]() __attribute__((always_inline)) { fetch(j1, w1); });
+      auto more = [&]() __attribute__((always_inline)) { fetch(j1, w1); };
+      gather_eight<LANES, 0>(Mc, off, w, lane_off, rn, acc, more);
       if constexpr (LANES > 8)
-        if (run > 8) gather_eight<LANES, 8>(Mc, off, w, lane_off, have, least, run, acc, [] {});
+        if (rn.run > 8) gather_eight<LANES, 8>(Mc, off, w, lane_off, rn, acc, [] {});
       if constexpr (LANES > 16) {
-        if (run > 16) gather_eight<LANES, 16>(Mc, off, w, lane_off, have, least, run, acc, [] {});
-        if (run > 24) gather_eight<LANES, 24>(Mc, off, w, lane_off, have, least, run, acc, [] {});
+        if (rn.run > 16) gather_eight<LANES, 16>(Mc, off, w, lane_off, rn, acc, [] {});
+        if (rn.run > 24) gather_eight<LANES, 24>(Mc, off, w, lane_off, rn, acc, [] {});
       }
       done += 64;
     } while (done < len);
@@ -330,7 +257,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, cons
       if (!mine) continue;
       acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-      for (int q = 0; q < kWavesPerBlock; ++q) Vec<4>::add(acc, *reinterpret_cast<const float4*>(sp + q * 4 * LANES));
+      for (int q = 0; q < kWalkWaves; ++q) Vec<4>::add(acc, *reinterpret_cast<const float4*>(sp + q * 4 * LANES));
     }
     if (!mine) continue;
     Vec<4>::add(acc, part);
@@ -356,14 +283,14 @@ __global__ void __launch_bounds__(kBlockThreads) k_agg_blocked(AggParams p, cons
 
 // One slice per long row: its chunk sums in chunk order, then the epilogue.
 template <int LANES, int EPI>
-__global__ void __launch_bounds__(kBlockThreads) k_finish_long(AggParams p, LongRows lr) {
+__global__ void __launch_bounds__(kWalkThreads) k_finish_long(AggParams p, LongRows lr) {
   Lanes L;
   L.gw = LANES;
   L.lig = threadIdx.x & (LANES - 1);
   L.slot = 0;
   L.lane = L.lig;
   L.c0 = ((int)blockIdx.y * LANES + L.lane) * 4;
-  const int64_t o = ((int64_t)blockIdx.x * kBlockThreads + threadIdx.x) / LANES;
+  const int64_t o = ((int64_t)blockIdx.x * kWalkThreads + threadIdx.x) / LANES;
   if (o >= lr.sp.n_long) return;
   const bool cok = L.c0 < p.w;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -409,14 +336,14 @@ __global__ void __launch_bounds__(256) k_block_pieces(int32_t n, const int64_t* 
 // The loss epilogue over the finished sums in Z (a whole row per slice), where a row takes
 // several panels.
 template <int LANES>
-__global__ void __launch_bounds__(kBlockThreads) k_finish_softmax(AggParams p) {
+__global__ void __launch_bounds__(kWalkThreads) k_finish_softmax(AggParams p) {
   Lanes L;
   L.gw = LANES;
   L.lig = threadIdx.x & (LANES - 1);
   L.slot = 0;
   L.lane = L.lig;
   L.c0 = 4 * L.lane;
-  const int64_t row = ((int64_t)blockIdx.x * kBlockThreads + threadIdx.x) / LANES;
+  const int64_t row = ((int64_t)blockIdx.x * kWalkThreads + threadIdx.x) / LANES;
   if (row >= p.n) return;
   const bool cok = L.c0 < p.w;
   const float4 acc = cok ? *reinterpret_cast<const float4*>(p.Z + row * p.ldz + L.c0) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -430,17 +357,17 @@ gcn_status run_blocks(const AggParams& p, const BlockedPlan& b, const Piece* pie
   // chip on small graphs and keep its end short (2 against 1 and 4: within 2 % on large ones)
   const int most = b.nblock > 1 || EPI == AGG_SOFTMAX ? kMaxRounds : 2;
   const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(most, (int64_t)p.n * panels / 32768));
-  const dim3 grid((unsigned)(lr.groups + ceil_div(p.n, (int64_t)rounds * kWavesPerBlock)), (unsigned)panels);
+  const dim3 grid((unsigned)(lr.groups + ceil_div(p.n, (int64_t)rounds * kWalkWaves)), (unsigned)panels);
   for (int32_t c = 0; c < b.nblock; ++c) {
     if (c == b.nblock - 1)
-      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI>), grid, dim3(kBlockThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
+      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
     else
-      hipLaunchKernelGGL((k_agg_blocked<LANES, AGG_NONE>), grid, dim3(kBlockThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
+      hipLaunchKernelGGL((k_agg_blocked<LANES, AGG_NONE>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
     GCN_TRY(check_launch("blocked aggregation"));
   }
   if (lr.groups > 0) {
-    hipLaunchKernelGGL((k_finish_long<LANES, EPI>), dim3((unsigned)ceil_div((int64_t)lr.sp.n_long * LANES, kBlockThreads), (unsigned)panels),
-                       dim3(kBlockThreads), 0, s, p, lr);
+    hipLaunchKernelGGL((k_finish_long<LANES, EPI>), dim3((unsigned)ceil_div((int64_t)lr.sp.n_long * LANES, kWalkThreads), (unsigned)panels),
+                       dim3(kWalkThreads), 0, s, p, lr);
     GCN_TRY(check_launch("long rows"));
   }
   return GCN_OK;
@@ -459,8 +386,8 @@ gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* piec
   if (need <= LANES) return GCN_OK;
   auto finish = [&](auto ln) {
     constexpr int LN = decltype(ln)::value;
-    hipLaunchKernelGGL(k_finish_softmax<LN>, dim3((unsigned)ceil_div((int64_t)p.n * LN, kBlockThreads)),
-                       dim3(kBlockThreads), 0, s, p);
+    hipLaunchKernelGGL(k_finish_softmax<LN>, dim3((unsigned)ceil_div((int64_t)p.n * LN, kWalkThreads)),
+                       dim3(kWalkThreads), 0, s, p);
     return check_launch("softmax epilogue");
   };
   if (need <= 32) return finish(std::integral_constant<int, 32>{});
@@ -472,6 +399,11 @@ gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* piec
 // Panel and block of an aggregation of n rows with nnz entries from src_rows rows of M (pitch
 // ldm), w columns.  All lines measured with Chung-Lu graphs of 5,000 to 1,000,000 rows and 8 to
 // 490 entries per row.
+//
+// Up to 16 columns: slices of 4 lanes, but where many rows of few entries would leave most of a
+// wavefront idle, the lane groups of aggregate.hip (1,000,000 rows of 8, width 7: 172 us against
+// 264; 200,000 rows of 32 125 against 71; 100,000 of 8 41 against 32; 20,000 of 64, whose longest
+// row a group walks by itself, 38 against 17).
 //
 // Panel: one slice per row where the row fits (8 lanes up to 32 columns, 16 up to 64, 32 above);
 // wider rows that start at line boundaries take 64-column panels of two lines instead (width
@@ -489,7 +421,13 @@ gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* piec
 // 128, width 24: 406 against 464; 100,000 of 128: 203 against 176).
 BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w, int64_t ldm, bool may_block) {
   BlockedPlan b{};
-  if (n <= 0 || nnz < 0 || src_rows <= 0 || w <= 16 || 4 * src_rows * ldm > (int64_t)UINT32_MAX) return b;
+  if (w <= 0 || n <= 0 || nnz < 0 || src_rows <= 0 || 4 * src_rows * ldm > (int64_t)UINT32_MAX) return b;
+  if (w <= 16) {
+    if (nnz < 16 * n && n > 400000) return b;
+    b.lanes = 4;
+    b.nblock = 1;
+    return b;
+  }
   const bool lines = ldm % 32 == 0;
   b.lanes = w <= 32 ? 8 : (w <= 64 || lines ? 16 : 32);
   b.nblock = 1;
@@ -532,9 +470,10 @@ gcn_status launch_agg_blocked(const AggParams& p, const BlockedPlan& b, const gc
     lr.sp = *split;
     lr.part = static_cast<float*>(ws);
     lr.pw = round_up(p.w, 4);
-    lr.groups = (int32_t)ceil_div(split->n_chunk, kWavesPerBlock);
+    lr.groups = (int32_t)ceil_div(split->n_chunk, kWalkWaves);
   }
   switch (b.lanes) {
+    case 4: return run_lanes<4>(p, b, pieces, lr, s);
     case 8: return run_lanes<8>(p, b, pieces, lr, s);
     case 16: return run_lanes<16>(p, b, pieces, lr, s);
     default: return run_lanes<32>(p, b, pieces, lr, s);

@@ -107,7 +107,7 @@ struct AggParams {
 };
 // Words per row of a ReLU bitmask of width w.
 inline int64_t relu_bits_words(int32_t w) { return (w + 31) / 32; }
-// The form of 16-byte rows wider than 16 columns (agg_blocked.hip): panels of 4 * lanes columns;
+// The form of 16-byte rows (agg_blocked.hip): panels of 4 * lanes columns;
 // nblock > 1: blocked by source rows, `rows` rows of M each; nblock == 0: not taken.
 struct BlockedPlan {
   int lanes;

@@ -825,7 +825,7 @@ def test_wide_row_panels(G, orc, n, e, blocked):
     bias = rng.standard_normal(260).astype(np.float32)
     mask = rng.standard_normal((n, 260)).astype(np.float32)
     kinds = {"norm": G.AGG_NORM, "sum": G.AGG_SUM, "mean": G.AGG_MEAN, "mean_t": G.AGG_MEAN_T}
-    for w, ld in ((17, 20), (32, 32), (33, 48), (64, 64), (65, 68), (100, 100), (128, 128), (129, 132), (256, 256),
+    for w, ld in ((1, 4), (5, 8), (16, 16), (17, 20), (32, 32), (33, 48), (64, 64), (65, 68), (100, 100), (128, 128), (129, 132), (256, 256),
                   (260, 288)):
         for kind, epi in (("norm", G.EPI_NONE), ("norm", G.EPI_RELU), ("sum", G.EPI_MASK), ("mean", G.EPI_RELU),
                           ("mean_t", G.EPI_NONE)):
@@ -921,3 +921,35 @@ def test_build_csr_row_lengths(G, orc, n):
         with pytest.raises(G.GcnError) as e:
             G.build_csr(n, dev(s), dev(d2))
         assert e.value.status == G.E_RANGE
+
+
+@pytest.mark.parametrize("w,ld", [(17, 20), (33, 36), (64, 64), (100, 100), (128, 128), (256, 256)])
+def test_max_row_panels(G, orc, w, ld):
+    """The max aggregation and its gradient one row per wavefront, at the edges of the panels, with
+    rows cut over four wavefronts, ties (small integers: the first maximiser of many), rows of
+    -inf and infinities: maxima and maximisers bit for bit, the gradient to fp32 rounding of its
+    sum of |terms|, masked and not."""
+    n = 6000
+    s, d = gs.chung_lu(n, 60000, seed=5, dmax=2500.0)
+    og, dg = orc.build_csr(n, s, d), G.build_csr(n, dev(s), dev(d))
+    assert og.deg.max() > 1024
+    rng = np.random.default_rng(w)
+    M = rng.integers(-3, 4, (n, w)).astype(np.float32)
+    M[:, 1] = -np.inf
+    M[17, 2] = np.inf
+    M[:, 3] = rng.standard_normal(n)
+    P, arg = orc.aggregate_max(og, M)
+    Pd = pitched(np.zeros((n, w), np.float32), ld)
+    argd = torch.full((n, ld), -7, dtype=torch.int32, device="cuda")[:, :w]
+    G.aggregate_max(dg, pitched(M, ld), Pd, argd)
+    np.testing.assert_array_equal(host(Pd), P.astype(np.float32))
+    np.testing.assert_array_equal(host(argd), arg)
+    dP = rng.standard_normal((n, w)).astype(np.float32)
+    mask = rng.standard_normal((n, w)).astype(np.float32)
+    want = orc.aggregate_max_backward(og, dP, arg)
+    mag = orc.aggregate_max_backward(og, np.abs(dP), arg)
+    for mk in (None, mask):
+        dM = pitched(np.full((n, w), np.nan, np.float32), ld)
+        G.aggregate_max_bwd(dg, pitched(dP, ld), argd, dM, mask=None if mk is None else pitched(mk, ld))
+        keep = 1.0 if mk is None else (mk > 0)
+        assert_mag_close(host(dM), want * keep, mag, f"max gradient width {w}")
