@@ -397,24 +397,27 @@ gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* piec
 }  // namespace
 
 // Panel and block of an aggregation of n rows with nnz entries from src_rows rows of M (pitch
-// ldm), w columns.  All lines measured with Chung-Lu graphs of 5,000 to 1,000,000 rows and 8 to
-// 490 entries per row.
+// ldm), w columns.  All lines measured with Chung-Lu graphs of 5,000 to 2,300,000 rows and 3 to
+// 490 entries per row; times in us, the lane groups of aggregate.hip first.
 //
-// Up to 16 columns: slices of 4 lanes, but where many rows of few entries would leave most of a
-// wavefront idle, the lane groups of aggregate.hip (1,000,000 rows of 8, width 7: 172 us against
-// 264; 200,000 rows of 32 125 against 71; 100,000 of 8 41 against 32; 20,000 of 64, whose longest
-// row a group walks by itself, 38 against 17).
+// Many rows of few entries leave most of a wavefront idle, and narrow ones gather little: they
+// stay with the lane groups, several rows to a wavefront (up to 16 columns 328,000 rows of 5 54
+// against 84, of 14 101 against 91; up to 32 columns 328,000 of 7 85 against 106, of 10 135
+// against 111; up to 64 columns of 3 68 against 98, of 5 125 against 104).  On fewer rows the
+// longest row decides, which a lane group walks by itself (20,000 of 65, width 7: 38 against 17).
 //
-// Panel: one slice per row where the row fits (8 lanes up to 32 columns, 16 up to 64, 32 above);
-// wider rows that start at line boundaries take 64-column panels of two lines instead (width
-// 256, 169,343 rows: 306 us against 335; RMAT 2^21 rows 7,170 against 7,718), since half of the
-// panel fits the L2 twice; where rows are not line-aligned a narrower panel would fetch its edge
-// lines twice (width 100, 2,449,029 rows: 8,790 us in one panel, 12,900 in two).  32-column
+// Panel: one slice per row where the row fits (4 lanes up to 16 columns, 8 up to 32, 16 up to 64,
+// 32 above); wider rows that start at line boundaries take 64-column panels of two lines
+// instead (width 256, 169,343 rows of 15: 306 against 335 with 32 lanes; RMAT 2^21 rows of 31
+// 7,170 against 7,718), since half of the panel fits the L2 twice, unless a row has too few
+// entries to pay for a second walk (1,000,000 rows of 3, width 128: 715; width 100 in one panel
+// 405; lane groups 476 and 461).  Where rows are not line-aligned a narrower panel would fetch
+// its edge lines twice (width 100, 2,449,029 rows: 8,790 in one panel, 12,900 in two).  32-column
 // panels pay where rows are gathered often and M is between the L2's size and a few times that
-// (100,000 rows of 64: 564 us against 671; 50,000 of 32: 145 against 152; of 8: 106 against 63).
+// (100,000 rows of 64: 564 against 671; 50,000 of 32: 145 against 152; of 8: 106 against 63).
 //
 // Blocks: 6 MB panels of M (R1) where a row has 24 entries per block, else 12 MB ones (R2) where
-// it has 24 (100,000 rows of 128 entries, width 256: 957 us with R1, 1,047 unblocked; 200,000 of
+// it has 24 (100,000 rows of 128 entries, width 256: 957 with R1, 1,047 unblocked; 200,000 of
 // 128: 2,429 with R2, 2,713 unblocked; of 64: 1,594 against 1,416).  With 32 lanes the entries
 // are twice the bytes and 12 suffice for R2 (200,000 of 128, width 100: 1,205 against 1,612).
 // Rows of one line (8 lanes) gain from larger blocks alone, and from 2^17 rows on (200,000 of
@@ -422,14 +425,17 @@ gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* piec
 BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w, int64_t ldm, bool may_block) {
   BlockedPlan b{};
   if (w <= 0 || n <= 0 || nnz < 0 || src_rows <= 0 || 4 * src_rows * ldm > (int64_t)UINT32_MAX) return b;
+  const double avg = (double)nnz / (double)n;
+  if (w <= 16 ? (n > 131072 && avg < 12) || (n > 400000 && avg < 16) : n > 65536 && (w <= 32 ? avg < 8 : w <= 64 && avg < 4))
+    return b;
   if (w <= 16) {
-    if (nnz < 16 * n && n > 400000) return b;
     b.lanes = 4;
     b.nblock = 1;
     return b;
   }
   const bool lines = ldm % 32 == 0;
-  b.lanes = w <= 32 ? 8 : (w <= 64 || lines ? 16 : 32);
+  const bool halves = lines && ((n <= 400000 && avg >= 12) || avg >= 24);  // 64 of more than 64 columns
+  b.lanes = w <= 32 ? 8 : (w <= 64 || halves ? 16 : 32);
   b.nblock = 1;
   auto entries = [&](int64_t rows) { return (double)nnz / ((double)n * (double)ceil_div(src_rows, rows)); };
   if (may_block && src_rows <= INT32_MAX) {
@@ -450,7 +456,7 @@ BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w
   }
   // M in the L2 as it is (the weight of a sparse first layer): fewer passes over the entries
   if (w > 64 && n >= 32768 && 4 * src_rows * ldm <= (3 << 20)) b.lanes = 32;
-  if (lines && w > 64 && nnz >= 32 * n && src_rows >= 32768 && src_rows <= 400000) b.lanes = 8;
+  if (lines && w > 64 && avg >= 32 && src_rows >= 32768 && src_rows <= 400000) b.lanes = 8;
   return b;
 }
 

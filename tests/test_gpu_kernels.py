@@ -803,7 +803,7 @@ def test_gemm_bf16x6_matches_native_fp32(G, op, shape, monkeypatch):
     print(f"bf16x6 vs fp32 {op} {shape}: max |diff| / scale = {worst:.2e}")
 
 
-@pytest.mark.parametrize("n,e,blocked", [(30000, 1100000, True), (30000, 200000, False), (70, 400, False)])
+@pytest.mark.parametrize("n,e,blocked", [(30000, 1100000, True), (30000, 450000, False), (30000, 200000, False), (70, 400, False)])
 def test_wide_row_panels(G, orc, n, e, blocked):
     """The panelled aggregation at the edges of its panels (32, 64 and 128 columns; pitches that
     are and are not multiples of a line), for every weight kind and epilogue, unblocked and
