@@ -225,7 +225,8 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
     float* z = (chunks ? lr.part + row * lr.pw : p.Z + (int64_t)(row < 0 ? 0 : row) * p.ldz) + L.c0;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float4 part = acc, mk = acc;
-    if (!first && cok && L.slot == 0 && mine) part = *reinterpret_cast<const float4*>(z);
+    // (the loss epilogue keeps a row's sum in any slice, the others in slice 0)
+    if (!first && cok && (EPI == AGG_SOFTMAX || L.slot == 0) && mine) part = *reinterpret_cast<const float4*>(z);
     if (EPI == AGG_MASK && last && !chunks && cok && L.slot == 0 && mine)
       mk = *reinterpret_cast<const float4*>(p.mask + (int64_t)row * p.ldmask + L.c0);
     int done = 0;

@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import gcn_synth as gs
-from helpers import adversarial_graphs, assert_mag_close, messy
+from helpers import adversarial_graphs, assert_mag_close, assert_norm_close, messy
 
 pytestmark = pytest.mark.gpu
 
@@ -854,6 +854,34 @@ def test_wide_row_panels(G, orc, n, e, blocked):
     got = host(Z)
     np.testing.assert_array_equal(np.isinf(got[:, 3]), hit)
     assert np.isfinite(np.delete(got, 3, axis=1)).all() and not np.isnan(got).any()
+
+
+@pytest.mark.parametrize("agg", ["gcn", "mean"])
+@pytest.mark.parametrize("w", [7, 24, 33, 41, 64, 100, 128, 129, 256])
+def test_loss_epilogue_row_panels(G, orc, w, agg):
+    """The loss epilogue over sums that come from several blocks of source rows (33 columns and
+    more here), in slices of 16 and 32 lanes that each keep a row of their own, and over several
+    panels (64 columns and more than 128).  W is a cut of the identity, so the aggregated matrix is
+    the input's first columns.  Logits of every row relative to the sum of |terms|, the gradient
+    relative to its largest element, 1e-4 as everywhere here."""
+    n, f = 30000, 260
+    s, d = gs.chung_lu(n, 1100000, seed=5, dmax=6000.0)
+    og, dg = orc.build_csr(n, s, d), G.build_csr(n, dev(s), dev(d))
+    assert og.nnz / (n * 2) >= 24
+    rng = np.random.default_rng(w)
+    H = rng.standard_normal((n, f)).astype(np.float32)
+    b = rng.standard_normal(w).astype(np.float32)
+    y = rng.integers(0, w, n).astype(np.int32)
+    kind = G.AGG_NORM if agg == "gcn" else G.AGG_MEAN
+    L = G.make_layer(f, w, f, G.pitch(w), G.ACT_SOFTMAX_CE, 1, agg=kind)
+    Hout, logits, loss = G.padded(n, w), G.padded(n, w), torch.zeros(1, device="cuda")
+    G.layer_fwd(dg, L, dev(H), None, dev(np.eye(f, w, dtype=np.float32)), dev(b), Hout, labels=dev(y), loss=loss,
+                logits=logits)
+    Z, mag = orc.aggregate(og, H[:, :w], b, want_mag=True, kind=agg)
+    assert_mag_close(host(logits), Z, mag, f"{agg} logits {w}")
+    want, Gl, _ = orc.softmax_ce(Z, y)
+    assert float(host(loss)[0]) == pytest.approx(want, rel=1e-4)
+    assert_norm_close(host(Hout), Gl, f"{agg} loss gradient {w}")
 
 
 @pytest.mark.parametrize("f,ld", [(1, 1), (31, 32), (33, 33), (128, 128), (257, 260), (1025, 1028), (4097, 4097),
