@@ -429,6 +429,9 @@ BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w
   const double avg = (double)nnz / (double)n;
   if (w <= 16 ? (n > 131072 && avg < 12) || (n > 400000 && avg < 16) : n > 65536 && (w <= 32 ? avg < 8 : w <= 64 && avg < 4))
     return b;
+  // many entries of 64-byte rows beyond the L2s: the lane groups with the row order (284,480 rows
+  // of 306, width 16, layer both ways 1,912 here, 2,048 with one row per wavefront)
+  if (may_block && w <= 16 && n > 262144 && avg >= 128) return b;
   if (w <= 16) {
     b.lanes = 4;
     b.nblock = 1;
@@ -455,6 +458,10 @@ BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w
       return b;
     }
   }
+  // two panels of rows that share lines, unblocked: the lane groups with the row order (layer both
+  // ways, 717,618 rows of 176, width 152: 19,454 against 21,334; RMAT 2^19 rows of 33, width 246:
+  // 5,328 against 5,661)
+  if (may_block && w > 128 && !lines && n > 400000) return BlockedPlan{};
   // M in the L2 as it is (the weight of a sparse first layer): fewer passes over the entries
   if (w > 64 && n >= 32768 && 4 * src_rows * ldm <= (3 << 20)) b.lanes = 32;
   if (lines && w > 64 && avg >= 32 && src_rows >= 32768 && src_rows <= 400000) b.lanes = 8;
