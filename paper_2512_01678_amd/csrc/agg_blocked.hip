@@ -97,6 +97,18 @@ struct LongRows {
   int64_t pw;
   int32_t groups;
 };
+
+// A row's partial sum, this lane's `left` columns of it: what lies beyond the width is the caller's.
+__device__ __forceinline__ void store_sum(float* z, const float4& v, int left) {
+  if (left >= 4) {
+    *reinterpret_cast<float4*>(z) = v;
+  } else {
+    z[0] = v.x;
+    if (left > 1) z[1] = v.y;
+    if (left > 2) z[2] = v.z;
+  }
+}
+
 // The finished columns of one row (every slice holds them; slice 0 writes): ReLU with its
 // bitmask, or the mask (mk, this lane's columns of it).
 template <int LANES, int EPI>
@@ -263,7 +275,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
     if (!mine) continue;
     Vec<4>::add(acc, part);
     if (!last || chunks || (EPI == AGG_SOFTMAX && gridDim.y > 1)) {
-      if (cok && L.slot == 0) *reinterpret_cast<float4*>(z) = acc;
+      if (cok && L.slot == 0) store_sum(z, acc, chunks ? 4 : p.w - L.c0);
       continue;
     }
     if constexpr (EPI == AGG_SOFTMAX) {
@@ -300,7 +312,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_finish_long(AggParams p, LongR
       Vec<4>::add(acc, *reinterpret_cast<const float4*>(lr.part + ch * lr.pw + L.c0));
   const int64_t row = lr.sp.rows[o];
   if (EPI == AGG_SOFTMAX && gridDim.y > 1) {
-    if (cok) *reinterpret_cast<float4*>(p.Z + row * p.ldz + L.c0) = acc;
+    if (cok) store_sum(p.Z + row * p.ldz + L.c0, acc, p.w - L.c0);
   } else {
     finish_row<LANES, 4, EPI>(p, row, acc, L, cok);
   }

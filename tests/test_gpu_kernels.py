@@ -981,3 +981,56 @@ def test_max_row_panels(G, orc, w, ld):
         G.aggregate_max_bwd(dg, pitched(dP, ld), argd, dM, mask=None if mk is None else pitched(mk, ld))
         keep = 1.0 if mk is None else (mk > 0)
         assert_mag_close(host(dM), want * keep, mag, f"max gradient width {w}")
+
+
+def sentinel(a, ld, fill):
+    """Device copy of a with row pitch ld; the extra columns hold a finite value."""
+    buf = torch.full((a.shape[0], ld), fill, dtype=torch.float32, device="cuda")
+    buf[:, :a.shape[1]] = dev(a.astype(np.float32))
+    return buf[:, :a.shape[1]]
+
+
+def padding_of(t, ld):
+    return host(t.as_strided((t.shape[0], ld), (ld, 1)))[:, t.shape[1]:]
+
+
+@pytest.mark.parametrize("w,ld", [(17, 20), (33, 36), (41, 44), (41, 64), (47, 48), (101, 128), (602, 604)])
+def test_partial_sums_stay_inside_the_width(G, orc, w, ld):
+    """The columns between width and pitch are the caller's, also where a row's sum is built up in
+    Z by several launches (three blocks of source rows here): a finite value there, and another
+    one beside M, are found unchanged."""
+    n = 30000
+    s, d = gs.chung_lu(n, 1100000, seed=3, dmax=6000.0)
+    og, dg = orc.build_csr(n, s, d), G.build_csr(n, dev(s), dev(d))
+    rng = np.random.default_rng(w)
+    rows = rng.integers(0, n, 100)
+    M = rng.standard_normal((n, w)).astype(np.float32)
+    for epi in (G.EPI_NONE, G.EPI_RELU, G.EPI_MASK):
+        Z = sentinel(np.zeros((n, w)), ld, 12345.0)
+        mask = sentinel(np.ones((n, w)), ld, 1.0)
+        G.aggregate(dg, sentinel(M, ld, 7.0), Z, epi=epi, mask=mask if epi == G.EPI_MASK else None)
+        np.testing.assert_array_equal(padding_of(Z, ld), 12345.0)
+        want, mag = orc.aggregate(og, M, rows=rows, want_mag=True)
+        assert_mag_close(host(Z)[rows], np.maximum(want, 0) if epi == G.EPI_RELU else want, mag, f"width {w} pitch {ld}")
+
+
+@pytest.mark.parametrize("n,e", [(30000, 1100000), (30000, 450000)])
+@pytest.mark.parametrize("fi,fo,order", [(64, 41, "TF"), (130, 129, "TF"), (130, 101, "TF"), (130, 64, "AF")])
+def test_layer_outputs_stay_inside_the_width(G, orc, n, e, fi, fo, order):
+    """The same for a layer's outputs: the gradient row of the loss epilogue (one panel and two;
+    rows of more than 4,096 entries summed in chunks where the graph is not blocked), its logits,
+    and the saved aggregate of an aggregate-first layer."""
+    s, d = gs.chung_lu(n, e, seed=5, dmax=7000.0)
+    dg = G.build_csr(n, dev(s), dev(d))
+    assert dg.n_long > 0
+    rng = np.random.default_rng(fo)
+    H, W = rng.standard_normal((n, fi)), rng.standard_normal((fi, fo)) / np.sqrt(fi)
+    ldi, ldo = (fi + 3) // 4 * 4, (fo + 3) // 4 * 4
+    act = G.ACT_SOFTMAX_CE if order == "TF" else G.ACT_RELU
+    L = G.make_layer(fi, fo, ldi, ldo, act, 1, G.TRANSFORM_FIRST if order == "TF" else G.AGGREGATE_FIRST)
+    out, logits = sentinel(np.zeros((n, fo)), ldo, 12345.0), sentinel(np.zeros((n, fo)), ldo, 12345.0)
+    saved = sentinel(np.zeros((n, fi)), ldi, 12345.0)
+    G.layer_fwd(dg, L, sentinel(H, ldi, 7.0), None, dev(W.astype(np.float32)), dev(np.zeros(fo, np.float32)), out, saved=saved,
+                labels=dev(rng.integers(0, fo, n).astype(np.int32)), loss=torch.zeros(1, device="cuda"), logits=logits)
+    for t, ld in ((out, ldo), (logits, ldo), (saved, ldi)):
+        np.testing.assert_array_equal(padding_of(t, ld), 12345.0)
