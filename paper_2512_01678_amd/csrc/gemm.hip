@@ -520,11 +520,15 @@ int64_t pick_splits(const GemmParams& p, Shape sh) {
   // about 2048 wavefronts in all (measured best for wide and narrow tiles alike), each
   // workgroup walking at least 256 rows of k; of a small output (whose partials cost little)
   // at least 64, since a slab's latency then is the time: 16 x 7 over 2,708 rows, the
-  // whole call, 19.9 -> 13.3 us, 128 x 128 over 4,000 23.3 -> 14.4, over 100,000 the same
+  // whole call, 19.9 -> 13.3 us, 128 x 128 over 4,000 23.3 -> 14.4, over 100,000 the same.  From
+  // 129 rows on: two slabs one after the other cost less than the reduction's launch (80 rows, 16 x
+  // 7, in a graph 6.5 us whole, 7.2 cut; 100 8.4 and 8.1, but 2.9 us more of the host for the second
+  // launch; 140 10.0 and 7.5).  A split product has no epilogue: those stay whole up to 256 rows.
   const int64_t tiles = ceil_div(p.m, sh.bm) * ceil_div(p.n, sh.bn);
   const int64_t waves = sh.bn >= 256 ? 8 : (sh.bn >= 128 ? 4 : sh.bm / 64);
   int64_t s = ceil_div(GCN_TN_WAVES, tiles * waves);
-  const int64_t max_s = ceil_div(p.k, p.m * p.n <= 16384 ? 64 : 256);
+  const bool fine = p.m * p.n <= 16384 && p.k > 128 && p.epi == GEMM_NONE;
+  const int64_t max_s = ceil_div(p.k, fine ? 64 : 256);
   if (s > max_s) s = max_s;
   return s < 1 ? 1 : s;
 }

@@ -1034,3 +1034,20 @@ def test_layer_outputs_stay_inside_the_width(G, orc, n, e, fi, fo, order):
                 labels=dev(rng.integers(0, fo, n).astype(np.int32)), loss=torch.zeros(1, device="cuda"), logits=logits)
     for t, ld in ((out, ldo), (logits, ldo), (saved, ldi)):
         np.testing.assert_array_equal(padding_of(t, ld), 12345.0)
+
+
+@pytest.mark.parametrize("k", [1, 64, 65, 100, 128, 129, 200, 256])
+def test_gemm_short_reduction_with_epilogue(G, k):
+    """A^T B over up to 256 rows takes the ReLU and mask epilogues (a longer reduction may be split
+    over workgroups, which applies the bias only)."""
+    rng = np.random.default_rng(k)
+    for m, n in ((16, 7), (128, 128), (100, 47)):
+        A, B = rng.standard_normal((k, m)).astype(np.float32), rng.standard_normal((k, n)).astype(np.float32)
+        bias, mask = rng.standard_normal(n).astype(np.float32), rng.standard_normal((m, n)).astype(np.float32)
+        A64, B64 = A.astype(np.float64), B.astype(np.float64)
+        Z, mag = A64.T @ B64 + bias, np.abs(A64).T @ np.abs(B64) + np.abs(bias)
+        for epi in (G.EPI_NONE, G.EPI_RELU, G.EPI_MASK):
+            out = torch.full((m, n), float("nan"), device="cuda")
+            G.gemm(G.OP_TN, dev(A), dev(B), out, bias=dev(bias), epi=epi, mask=dev(mask) if epi == G.EPI_MASK else None)
+            want = Z if epi == G.EPI_NONE else (np.maximum(Z, 0) if epi == G.EPI_RELU else Z * (mask > 0))
+            assert_mag_close(host(out), want, mag, f"TN {m}x{n}x{k} epi {epi}")
