@@ -182,7 +182,8 @@ typedef struct gcn_layer {
  * non-NULL the hub split plan is built too (g->split.order is left NULL); when
  * g->order is non-NULL the row order is written (see gcn_graph).
  * Errors: GCN_E_RANGE if an endpoint is outside [0, n) (outputs undefined),
- * GCN_E_CAPACITY if nnz > nnz_cap or the workspace is short.
+ * GCN_E_CAPACITY if nnz > nnz_cap or the workspace is short, GCN_E_OVERFLOW for
+ * n > 2^30 or n_edges >= 2^30.
  */
 gcn_status gcn_build_csr(int32_t n, int64_t n_edges, const int32_t* d_src, const int32_t* d_dst,
                          gcn_graph* g, void* d_ws, size_t* ws_bytes, hipStream_t stream);

@@ -468,6 +468,7 @@ gcn_status gcn_build_csr(int32_t n, int64_t n_edges, const int32_t* d_src, const
   if (n < 0 || n_edges < 0) return fail(GCN_E_INVALID, "gcn_build_csr: negative size");
   if (n_edges >= (int64_t(1) << 30))
     return fail(GCN_E_OVERFLOW, "gcn_build_csr: more than 2^30 input pairs (row counts are int32)");
+  if (n > kMaxGraphRows) return fail(GCN_E_OVERFLOW, "gcn_build_csr: more than 2^30 nodes");
   bool query = false;
   GCN_TRY(ws_protocol(d_ws, ws_bytes, build_csr_workspace(n, n_edges), "gcn_build_csr", &query));
   if (query) return GCN_OK;

@@ -51,8 +51,8 @@ struct Parts {
   int64_t buckets, subs, nw;
 };
 
-Parts make_parts(int32_t n, int64_t n_edges) {
-  Parts q;
+constexpr Parts make_parts(int32_t n, int64_t n_edges) {
+  Parts q{};
   const double avg = n > 0 ? 2.0 * (double)n_edges / n + 1.0 : 1.0;
   q.s2 = 0;
   while (q.s2 < 10 && avg * (double)(int64_t(2) << q.s2) <= 7000.0) ++q.s2;
@@ -66,6 +66,14 @@ Parts make_parts(int32_t n, int64_t n_edges) {
   q.nw = std::max<int64_t>(1, std::min<int64_t>(512, ceil_div(n_edges, 4096)));
   return q;
 }
+// What the kernels hold in LDS: counters of one bucket's sub-buckets, of one sub-bucket's rows.
+constexpr bool parts_fit(int32_t n, int64_t n_edges) {
+  const Parts q = make_parts(n, n_edges);
+  return q.buckets <= kMaxBuckets && (1 << (q.s1 - q.s2)) <= kMaxBuckets && (1 << q.s2) <= kMaxSubRows;
+}
+static_assert(parts_fit(kMaxGraphRows, 0) && parts_fit(kMaxGraphRows, (1 << 30) - 1) && parts_fit(1 << 20, (1 << 30) - 1) &&
+                  parts_fit((1 << 20) + 1, 0) && parts_fit(1, 0) && parts_fit(0, 0),
+              "a bucket or sub-bucket outgrows its counters");
 
 struct Pair {
   int32_t row, col;

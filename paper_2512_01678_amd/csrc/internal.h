@@ -36,7 +36,7 @@ inline gcn_status check_launch(const char* what) {
     if (_e != hipSuccess) return hip_fail(_e, what); \
   } while (0)
 
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -234,6 +234,7 @@ gcn_status launch_colsum(int64_t rows, int32_t w, const float* G, int64_t ldg, f
 size_t scan_workspace(int64_t n);
 gcn_status launch_scan_i32(const int32_t* in, int64_t n, int64_t* out, void* ws, hipStream_t s);
 
+constexpr int32_t kMaxGraphRows = 1 << 30;  // rows that the graph build's two partition passes can tell apart
 size_t build_csr_workspace(int32_t n, int64_t n_edges);
 gcn_status run_build_csr(int32_t n, int64_t n_edges, const int32_t* src, const int32_t* dst,
                          gcn_graph* g, void* ws, hipStream_t s);

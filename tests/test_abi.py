@@ -73,6 +73,18 @@ def test_status_strings(G):
     assert L.gcn_version() >= 3
 
 
+def test_build_refuses_more_nodes_than_its_partition_tells_apart(G):
+    """More than 2^30 nodes would put 2,048 rows into sub-buckets whose counters hold 1,024: refused
+    by the size query and by the call, before anything is enqueued."""
+    L, nb = G.raw_lib(), G.sz(0)
+    assert L.gcn_build_csr(1 << 30, 5, None, None, None, None, C.byref(nb), None) == G.OK
+    for n in ((1 << 30) + 1, (1 << 31) - 1):
+        g, have = G.gcn_graph(n, 0, 100, 1, 1, 1, 1, 1), G.sz(1 << 50)
+        assert L.gcn_build_csr(n, 5, None, None, None, None, C.byref(nb), None) == G.E_OVERFLOW
+        assert L.gcn_build_csr(n, 5, 1, 1, C.byref(g), 1, C.byref(have), None) == G.E_OVERFLOW
+        assert "2^30" in L.gcn_last_error().decode()
+
+
 def test_host_validation_rejects_bad_calls(G):
     L = G.raw_lib()
     nb = G.sz(0)
