@@ -296,14 +296,15 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows(int32_t n, int s2, const 
                                                        int32_t* raw, int64_t* raw_off, int32_t* cnt, int32_t* deg,
                                                        int32_t* lists, int32_t* flags) {
   constexpr int U = 4;
-  __shared__ int32_t len[kMaxSubRows], cur[kMaxSubRows];
+  __shared__ int32_t len[kMaxSubRows];
+  __shared__ uint32_t cur[kMaxSubRows];  // up to 2 E + rows, just beyond 2^31 at the most
   __shared__ int32_t buf[kRowsCap];
   const int32_t r0 = (int32_t)((int64_t)blockIdx.x << s2);
   const int32_t rows = n - r0 < (1 << s2) ? n - r0 : 1 << s2;
   const int32_t lo = (int32_t)sub_off[blockIdx.x * stride], hi = (int32_t)sub_off[(blockIdx.x + 1) * stride];
   const int64_t base = (int64_t)lo + r0;  // every row before has its self entry
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-  const bool fits = hi - lo + rows <= kRowsCap;
+  const bool fits = (int64_t)hi - lo + rows <= kRowsCap;
   for (int r = threadIdx.x; r < rows; r += kRowsThreads) len[r] = 1;
   __syncthreads();
   auto each = [&](auto g) {
@@ -319,13 +320,13 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows(int32_t n, int s2, const 
   each([&](const Pair& p) { atomicAdd(&len[p.row - r0], 1); });
   __syncthreads();
   if (wave == 0) {  // exclusive scan of the rows' lengths
-    int32_t run = 0;
+    uint32_t run = 0;
     for (int q0 = 0; q0 < rows; q0 += 64) {
       const int q = q0 + lane;
-      const int32_t c = q < rows ? len[q] : 0;
-      int32_t incl = c;
+      const uint32_t c = q < rows ? (uint32_t)len[q] : 0u;
+      uint32_t incl = c;
       for (int o = 1; o < 64; o <<= 1) {
-        const int32_t up = __shfl_up(incl, o, 64);
+        const uint32_t up = __shfl_up(incl, o, 64);
         if (lane >= o) incl += up;
       }
       if (q < rows) cur[q] = run + incl - c;
@@ -336,7 +337,7 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows(int32_t n, int s2, const 
   int32_t* const seg = raw + base;
   // each row's self entry first, then its columns as they come; afterwards cur[r] is its end
   for (int r = threadIdx.x; r < rows; r += kRowsThreads) {
-    const int32_t at = cur[r];
+    const uint32_t at = cur[r];
     cnt[r0 + r] = len[r];
     raw_off[r0 + r] = base + at;
     if (fits) buf[at] = r0 + r;
@@ -344,11 +345,12 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows(int32_t n, int s2, const 
     cur[r] = at + 1;
   }
   __syncthreads();
-  if (fits) each([&](const Pair& p) { buf[atomicAdd(&cur[p.row - r0], 1)] = p.col; });
-  else each([&](const Pair& p) { seg[atomicAdd(&cur[p.row - r0], 1)] = p.col; });
+  if (fits) each([&](const Pair& p) { buf[atomicAdd(&cur[p.row - r0], 1u)] = p.col; });
+  else each([&](const Pair& p) { seg[atomicAdd(&cur[p.row - r0], 1u)] = p.col; });
   __syncthreads();
   for (int r = wave; r < rows; r += kRowsThreads / 64) {
-    const int32_t l = len[r], at = cur[r] - l;
+    const int32_t l = len[r];
+    const uint32_t at = cur[r] - (uint32_t)l;
     const int32_t* from = fits ? buf + at : seg + at;
     if (l <= kSmall) {
       const int32_t d = l <= 64    ? sort_row<1>(from, seg + at, l, lane)

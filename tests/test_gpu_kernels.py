@@ -4,12 +4,14 @@ Integer / index work (CSR build, degrees, dinv, nonzero counts, compressed
 feature views) must match bit for bit; fp32 results must stay within 1e-4 of
 the oracle relative to each element's magnitude scale (sum of |terms|).
 """
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
 import gcn_synth as gs
-from helpers import adversarial_graphs, assert_mag_close, assert_norm_close, messy
+from helpers import adversarial_graphs, assert_mag_close, assert_norm_close, messy, note
 
 pytestmark = pytest.mark.gpu
 
@@ -1051,3 +1053,24 @@ def test_gemm_short_reduction_with_epilogue(G, k):
             G.gemm(G.OP_TN, dev(A), dev(B), out, bias=dev(bias), epi=epi, mask=dev(mask) if epi == G.EPI_MASK else None)
             want = Z if epi == G.EPI_NONE else (np.maximum(Z, 0) if epi == G.EPI_RELU else Z * (mask > 0))
             assert_mag_close(host(out), want, mag, f"TN {m}x{n}x{k} epi {epi}")
+
+
+def test_build_csr_all_pairs_in_one_sub_bucket(G):
+    """The largest input there is, 2^30 - 1 pairs, all of the nodes 0 and 1, which share a sub-bucket
+    of the partition: 2^31 raw entries there, one more than 31 bits count."""
+    n, e = 700000, (1 << 30) - 1
+    s, d = torch.zeros(e, dtype=torch.int32, device="cuda"), torch.ones(e, dtype=torch.int32, device="cuda")
+    s[::3], d[::3] = 1, 0
+    L, g = G.raw_lib(), G.build_csr(n, s[:1], d[:1])
+    need = G.sz(0)
+    assert L.gcn_build_csr(n, e, None, None, None, None, C.byref(need), None) == G.OK
+    ws = torch.empty(need.value, dtype=torch.uint8, device="cuda")
+    g.row_ptr.fill_(-1)
+    note("2^30 - 1 pairs of two nodes")
+    rc = L.gcn_build_csr(n, e, s.data_ptr(), d.data_ptr(), C.byref(g.c), ws.data_ptr(), C.byref(need), None)
+    assert rc == G.OK, L.gcn_last_error()
+    note("built")
+    assert g.c.nnz == n + 2 and host(g.col_idx)[:5].tolist() == [0, 1, 0, 1, 2]
+    assert host(g.row_ptr[:4]).tolist() == [0, 2, 4, 5] and int(g.row_ptr[n]) == n + 2
+    want = np.float32(1 / np.sqrt(2))
+    np.testing.assert_array_equal(host(g.val)[:5], np.array([want * want] * 4 + [1.0], np.float32))
