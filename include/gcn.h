@@ -13,7 +13,11 @@
  *    memory; scratch space comes from a caller workspace (d_ws, *ws_bytes).
  *  - Workspace protocol: call with d_ws == NULL to have *ws_bytes set to the
  *    bytes needed (nothing is launched); then call again with a buffer of at
- *    least that size.  A smaller *ws_bytes gives GCN_E_CAPACITY.
+ *    least that size.  A smaller *ws_bytes gives GCN_E_CAPACITY, except that room
+ *    which only makes a call faster may be left out: the row pieces of an
+ *    aggregation that is blocked by source rows (gcn_aggregate, the layers and
+ *    gcn_epoch; 16 bytes per row and block) and one bit per element of X
+ *    (gcn_feature_stats).
  *  - Dense matrices are fp32, row-major, with a row pitch ld >= width given in
  *    elements.  Rows whose pitch is a multiple of 4 and whose base is 16-byte
  *    aligned take the vector path; anything else is still correct.  A buffer
@@ -315,7 +319,9 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
  * d_M: n x w (pitch ldm).  d_bias: w or NULL.  epi: GCN_EPI_NONE, GCN_EPI_RELU
  * (max(Z, 0)) or GCN_EPI_MASK (Z * 1[mask > 0], d_mask n x w, pitch ldmask).
  * d_Z: n x w (pitch ldz); must not overlap d_M.  The workspace holds the chunk
- * sums of split hub rows (g->split.n_chunk x w floats, rounded up).
+ * sums of split hub rows (g->split.n_chunk x w floats, rounded up) or, on a dense
+ * graph whose sums are blocked by source rows, the row pieces; with room for the
+ * chunk sums alone the sums are not blocked (the same to rounding).
  */
 gcn_status gcn_aggregate(const gcn_graph* g, int32_t agg, int32_t w, const float* d_M, int64_t ldm,
                          const float* d_bias, int32_t epi, const float* d_mask, int64_t ldmask,

@@ -27,8 +27,10 @@ gcn_status hip_fail(hipError_t e, const char* what) {
 
 namespace {
 
-// Workspace protocol: NULL buffer -> report size; else check it is large enough.
-gcn_status ws_protocol(void* d_ws, size_t* ws_bytes, size_t need, const char* who, bool* query) {
+// Workspace protocol: NULL buffer -> report size; else check it is large enough.  A call that
+// can do with less room than it reports (`least`) runs in that too.
+gcn_status ws_protocol(void* d_ws, size_t* ws_bytes, size_t need, const char* who, bool* query,
+                       size_t least = SIZE_MAX) {
   if (!ws_bytes) return fail(GCN_E_INVALID, std::string(who) + ": ws_bytes is NULL");
   if (!d_ws) {
     *ws_bytes = need;
@@ -36,6 +38,7 @@ gcn_status ws_protocol(void* d_ws, size_t* ws_bytes, size_t need, const char* wh
     return GCN_OK;
   }
   *query = false;
+  need = std::min(need, least);
   if (*ws_bytes < need)
     return fail(GCN_E_CAPACITY, std::string(who) + ": workspace of " + std::to_string(*ws_bytes) +
                                     " bytes, " + std::to_string(need) + " needed");
@@ -120,7 +123,7 @@ int32_t agg_transpose(int32_t agg) {
 }
 
 AggParams graph_agg(const gcn_graph* g, int32_t w, const float* M, int64_t ldm, float* Z, int64_t ldz,
-                    int32_t agg = GCN_AGG_NORM) {
+                    int32_t agg, bool may_block) {
   AggParams p{};
   p.deg = g->deg;
   p.kind = agg == GCN_AGG_SUM ? AGG_W_ONE
@@ -138,7 +141,7 @@ AggParams graph_agg(const gcn_graph* g, int32_t w, const float* M, int64_t ldm, 
   p.epi = AGG_NONE;
   p.order = g->order;
   p.src_rows = g->n;
-  p.may_block = true;
+  p.may_block = may_block;
   return p;
 }
 
@@ -211,7 +214,7 @@ gcn_status layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* Hin, c
     // With the softmax cross-entropy, Z = P W + b goes through the loss epilogue of an
     // aggregation over the identity operator.
     const bool softmax = L->act == GCN_ACT_SOFTMAX_CE;
-    void* aws = a.take<char>((int64_t)graph_aggregate_workspace(g, L->f_in, L->ld_in));
+    void* aws = a.take<char>((int64_t)graph_aggregate_workspace(g, L->f_in, L->ld_in, !a.lean));
     const int64_t ldz = gather_pitch(L->f_out);
     float* Zs = softmax ? a.take<float>((int64_t)n * ldz) : nullptr;
     int64_t* id_ptr = softmax ? a.take<int64_t>((int64_t)n + 1) : nullptr;
@@ -224,13 +227,13 @@ gcn_status layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* Hin, c
     q.bias = b;
     void* gws = a.take<char>((int64_t)gemm_workspace(q));
     if (run && L->agg == GCN_AGG_MAX) {
-      AggParams p = graph_agg(g, L->f_in, Hin, L->ld_in, saved, L->ld_in);
+      AggParams p = graph_agg(g, L->f_in, Hin, L->ld_in, saved, L->ld_in, L->agg, false);
       int32_t* arg = reinterpret_cast<int32_t*>(saved + (int64_t)n * L->ld_in);
       GCN_TRY(launch_aggregate_max(p, g->nnz, saved, L->ld_in, arg, L->ld_in, s));
     }
     if (run && softmax) {
       if (L->agg != GCN_AGG_MAX) {
-        AggParams p = graph_agg(g, L->f_in, Hin, L->ld_in, saved, L->ld_in, L->agg);
+        AggParams p = graph_agg(g, L->f_in, Hin, L->ld_in, saved, L->ld_in, L->agg, !a.lean);
         GCN_TRY(launch_aggregate(p, g->nnz, &g->split, aws, s));
       }
       GCN_TRY(launch_gemm(with_split(q, sj, nsj), gws, s));
@@ -264,7 +267,7 @@ gcn_status layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* Hin, c
     }
     if (!run) return GCN_OK;
     if (L->agg != GCN_AGG_MAX) {
-      AggParams p = graph_agg(g, L->f_in, Hin, L->ld_in, saved, L->ld_in, L->agg);
+      AggParams p = graph_agg(g, L->f_in, Hin, L->ld_in, saved, L->ld_in, L->agg, !a.lean);
       GCN_TRY(launch_aggregate(p, g->nnz, &g->split, aws, s));
     }
     return launch_gemm(with_split(q, sj, nsj), gws, s);
@@ -274,7 +277,7 @@ gcn_status layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* Hin, c
   float* M = a.take<float>((int64_t)n * ldm);
   float* row_loss = L->act == GCN_ACT_SOFTMAX_CE ? a.take<float>(n) : nullptr;
   void* cws = L->act == GCN_ACT_SOFTMAX_CE ? a.take<char>((int64_t)colsum_workspace(n, L->f_out)) : nullptr;
-  void* aws = a.take<char>((int64_t)graph_aggregate_workspace(g, L->f_out, ldm));
+  void* aws = a.take<char>((int64_t)graph_aggregate_workspace(g, L->f_out, ldm, !a.lean));
   const GemmParams q = gemm(n, L->f_out, L->f_in, Hin, L->ld_in, false, W, L->f_out, false, M, ldm);
   void* gws = x ? nullptr : a.take<char>((int64_t)gemm_workspace(q));
   if (bits_written) *bits_written = want_bits;  // the aggregation epilogue writes them
@@ -284,7 +287,7 @@ gcn_status layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* Hin, c
   } else {
     GCN_TRY(launch_gemm(with_split(q, sj, nsj), gws, s));
   }
-  AggParams p = graph_agg(g, L->f_out, M, ldm, Hout, L->ld_out, L->agg);
+  AggParams p = graph_agg(g, L->f_out, M, ldm, Hout, L->ld_out, L->agg, !a.lean);
   p.bias = b;
   if (L->act == GCN_ACT_RELU) p.epi = AGG_RELU;
   if (want_bits) {
@@ -326,7 +329,7 @@ gcn_status layer_bwd(const gcn_graph* g, const gcn_layer* L, const float* G, con
     void* gws = a.take<char>((int64_t)gemm_workspace(dw));
     const int64_t ldt = gather_pitch(L->f_in);
     float* T = Gprev ? a.take<float>((int64_t)n * ldt) : nullptr;
-    void* aws = Gprev ? a.take<char>((int64_t)graph_aggregate_workspace(g, L->f_in, ldt)) : nullptr;
+    void* aws = Gprev ? a.take<char>((int64_t)graph_aggregate_workspace(g, L->f_in, ldt, !a.lean)) : nullptr;
     const GemmParams t = gemm(n, L->f_in, L->f_out, G, L->ld_out, false, W, L->f_out, true, T, ldt);
     void* tws = Gprev ? a.take<char>((int64_t)gemm_workspace(t)) : nullptr;
     if (!run) return GCN_OK;
@@ -334,7 +337,7 @@ gcn_status layer_bwd(const gcn_graph* g, const gcn_layer* L, const float* G, con
     if (!db_ready) GCN_TRY(launch_colsum(n, L->f_out, G, L->ld_out, db, nullptr, nullptr, cws, s));
     if (Gprev) {
       GCN_TRY(launch_gemm(with_split(t, sj, nsj), tws, s));
-      AggParams p = graph_agg(g, L->f_in, T, ldt, Gprev, L->ld_in, agg_transpose(L->agg));
+      AggParams p = graph_agg(g, L->f_in, T, ldt, Gprev, L->ld_in, agg_transpose(L->agg), !a.lean);
       if (L->agg == GCN_AGG_MAX) {
         // each (G W^T)[v,c] goes back to the saved maximiser of (v, c)
         const int32_t* arg = reinterpret_cast<const int32_t*>(saved + (int64_t)n * L->ld_in);
@@ -353,7 +356,7 @@ gcn_status layer_bwd(const gcn_graph* g, const gcn_layer* L, const float* G, con
   float* Q = a.take<float>((int64_t)n * ldq);
   GemmParams dw = gemm(L->f_in, L->f_out, n, Hin, L->ld_in, true, Q, ldq, false, dW, L->f_out);
   void* gws = x ? nullptr : a.take<char>((int64_t)gemm_workspace(dw));
-  const size_t agg_need = std::max(graph_aggregate_workspace(g, L->f_out, L->ld_out),
+  const size_t agg_need = std::max(graph_aggregate_workspace(g, L->f_out, L->ld_out, !a.lean),
                                    x && x->col_ptr ? spmm_xt_workspace(n, x->f, x->nnz, L->f_out, &x->csc_split)
                                                    : (size_t)0);
   void* aws = a.take<char>((int64_t)agg_need);
@@ -376,7 +379,7 @@ gcn_status layer_bwd(const gcn_graph* g, const gcn_layer* L, const float* G, con
   }
   void* tws = Gprev ? a.take<char>((int64_t)gemm_workspace(t)) : nullptr;
   if (!run) return GCN_OK;
-  GCN_TRY(launch_aggregate(graph_agg(g, L->f_out, G, L->ld_out, Q, ldq, agg_transpose(L->agg)), g->nnz,
+  GCN_TRY(launch_aggregate(graph_agg(g, L->f_out, G, L->ld_out, Q, ldq, agg_transpose(L->agg), !a.lean), g->nnz,
                            &g->split, aws, s));
   if (x && !x->col_ptr) {
     // no CSC view: dW = X^T Q by atomic adds from the CSR rows (Section IV-D)
@@ -493,14 +496,16 @@ gcn_status gcn_feature_stats(const float* d_X, int32_t n, int32_t f, int64_t ldx
   if (force_mode < -1 || force_mode > GCN_SPARSE) return fail(GCN_E_INVALID, "gcn_feature_stats: bad force_mode");
   const bool csc = x && x->col_ptr;
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, feature_stats_workspace(n, f, x != nullptr, csc), "gcn_feature_stats", &query));
+  const size_t need = feature_stats_workspace(n, f, x != nullptr, csc);
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, need, "gcn_feature_stats", &query, feature_stats_workspace(n, f, false, csc)));
   if (query) return GCN_OK;
   if (!info || (n > 0 && f > 0 && !d_X)) return fail(GCN_E_INVALID, "gcn_feature_stats: X and info are required");
   if (x && (!x->row_ptr || !x->col || !x->val || (csc && (!x->row || !x->cval))))
     return fail(GCN_E_INVALID, "gcn_feature_stats: sparse output arrays missing");
   if (x && csc && x->csc_split.rows && (!x->csc_split.first || !x->csc_split.owner || x->csc_split.cap < 0))
     return fail(GCN_E_INVALID, "gcn_feature_stats: split plan arrays missing");
-  return run_feature_stats(d_X, n, f, ldx, tau_num, tau_den, force_mode, d_row_nnz, info, x, d_ws, stream);
+  return run_feature_stats(d_X, n, f, ldx, tau_num, tau_den, force_mode, d_row_nnz, info, x, x && *ws_bytes >= need, d_ws,
+                           stream);
 }
 
 gcn_status gcn_layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* d_Hin,
@@ -509,13 +514,16 @@ gcn_status gcn_layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* d_
                          void* d_ws, size_t* ws_bytes, hipStream_t stream) {
   g_err.clear();
   GCN_TRY(validate_fwd(g, L, d_Hin, x, d_W, d_Hout, d_saved, d_labels, d_loss, "gcn_layer_fwd"));
-  Arena plan;
+  Arena plan, least;
+  least.lean = true;
   GCN_TRY(layer_fwd(g, L, d_Hin, x, d_W, d_b, d_Hout, d_saved, d_labels, d_loss, d_logits, plan, stream));
+  GCN_TRY(layer_fwd(g, L, d_Hin, x, d_W, d_b, d_Hout, d_saved, d_labels, d_loss, d_logits, least, stream));
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, plan.used, "gcn_layer_fwd", &query));
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, plan.used, "gcn_layer_fwd", &query, least.used));
   if (query) return GCN_OK;
   Arena a;
   a.base = static_cast<char*>(d_ws);
+  a.lean = *ws_bytes < plan.used;
   return layer_fwd(g, L, d_Hin, x, d_W, d_b, d_Hout, d_saved, d_labels, d_loss, d_logits, a, stream);
 }
 
@@ -524,13 +532,16 @@ gcn_status gcn_layer_bwd(const gcn_graph* g, const gcn_layer* L, const float* d_
                          float* d_db, float* d_Gprev, void* d_ws, size_t* ws_bytes, hipStream_t stream) {
   g_err.clear();
   GCN_TRY(validate_bwd(g, L, d_G, d_Hin, x, d_saved, d_W, d_dW, d_db, d_Gprev, "gcn_layer_bwd"));
-  Arena plan;
+  Arena plan, least;
+  least.lean = true;
   GCN_TRY(layer_bwd(g, L, d_G, d_Hin, x, d_saved, d_W, d_dW, d_db, d_Gprev, plan, stream));
+  GCN_TRY(layer_bwd(g, L, d_G, d_Hin, x, d_saved, d_W, d_dW, d_db, d_Gprev, least, stream));
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, plan.used, "gcn_layer_bwd", &query));
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, plan.used, "gcn_layer_bwd", &query, least.used));
   if (query) return GCN_OK;
   Arena a;
   a.base = static_cast<char*>(d_ws);
+  a.lean = *ws_bytes < plan.used;
   return layer_bwd(g, L, d_G, d_Hin, x, d_saved, d_W, d_dW, d_db, d_Gprev, a, stream);
 }
 
@@ -567,7 +578,7 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
   uint32_t* const probe = reinterpret_cast<uint32_t*>((uintptr_t)256);
   float* const probe_db = reinterpret_cast<float*>((uintptr_t)256);
   bool writes[8] = {}, reads[8] = {}, sums[8] = {};  // sums[l]: layer l's backward can write db[l-1]
-  size_t need = 0;
+  size_t need = 0, least = 0;  // least: with lean arenas
   for (int l = 0; l < L; ++l) {
     const gcn_layer* ly = &m->layers[l];
     const float* Hin = l == 0 ? d_X : m->act[l - 1];
@@ -577,13 +588,17 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
     GCN_TRY(validate_fwd(g, ly, Hin, xl, m->W[l], Hout, saved, d_labels, d_loss, who));
     GCN_TRY(validate_bwd(g, ly, m->grad[l], Hin, xl, saved, m->W[l], m->dW[l], m->db[l],
                          l > 0 ? m->grad[l - 1] : nullptr, who));
-    Arena pf, pb;
-    GCN_TRY(layer_fwd(g, ly, Hin, xl, m->W[l], m->b[l], Hout, saved, d_labels, d_loss, nullptr, pf, stream,
-                      l < L - 1 ? probe : nullptr, &writes[l]));
-    GCN_TRY(layer_bwd(g, ly, m->grad[l], Hin, xl, saved, m->W[l], m->dW[l], m->db[l],
-                      l > 0 ? m->grad[l - 1] : nullptr, pb, stream, l > 0 ? probe : nullptr, &reads[l],
-                      l > 0 ? probe_db : nullptr, &sums[l]));
-    need = std::max(need, std::max(pf.used, pb.used));
+    for (const bool lean : {false, true}) {
+      Arena pf, pb;
+      pf.lean = pb.lean = lean;
+      GCN_TRY(layer_fwd(g, ly, Hin, xl, m->W[l], m->b[l], Hout, saved, d_labels, d_loss, nullptr, pf, stream,
+                        l < L - 1 ? probe : nullptr, &writes[l]));
+      GCN_TRY(layer_bwd(g, ly, m->grad[l], Hin, xl, saved, m->W[l], m->dW[l], m->db[l],
+                        l > 0 ? m->grad[l - 1] : nullptr, pb, stream, l > 0 ? probe : nullptr, &reads[l],
+                        l > 0 ? probe_db : nullptr, &sums[l]));
+      size_t& most = lean ? least : need;
+      most = std::max(most, std::max(pf.used, pb.used));
+    }
   }
   int64_t bits_at[8];
   size_t bits_bytes = 0;
@@ -622,8 +637,9 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
     }
   }
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, bits_bytes + need, who, &query));
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, bits_bytes + need, who, &query, bits_bytes + least));
   if (query) return GCN_OK;
+  const bool lean = *ws_bytes < bits_bytes + need;
   char* const base = static_cast<char*>(d_ws);
   auto bits_of = [&](int l) { return bits_at[l] < 0 ? nullptr : reinterpret_cast<uint32_t*>(base + bits_at[l]); };
   for (int q = 0; q < njobs; ++q) jobs[q].out = base + job_at[q];
@@ -631,6 +647,7 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
   for (int l = 0; l < L; ++l) {
     Arena a;
     a.base = base + bits_bytes;
+    a.lean = lean;
     const gcn_layer* ly = &m->layers[l];
     GCN_TRY(layer_fwd(g, ly, l == 0 ? d_X : m->act[l - 1], l == 0 ? x : nullptr, m->W[l], m->b[l],
                       l < L - 1 ? m->act[l] : m->grad[l], m->saved ? m->saved[l] : nullptr, d_labels,
@@ -645,6 +662,7 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
   for (int l = L - 1; l >= 0; --l) {
     Arena a;
     a.base = base + bits_bytes;
+    a.lean = lean;
     const gcn_layer* ly = &m->layers[l];
     const bool fuse_db = l > 0 && bits_at[l - 1] >= 0 && sums[l];
     GCN_TRY(layer_bwd(g, ly, m->grad[l], l == 0 ? d_X : m->act[l - 1], l == 0 ? x : nullptr,
@@ -675,10 +693,11 @@ gcn_status gcn_aggregate(const gcn_graph* g, int32_t agg, int32_t w, const float
   if (epi < GCN_EPI_NONE || epi > GCN_EPI_MASK) return fail(GCN_E_INVALID, "gcn_aggregate: unknown epilogue");
   if (epi == GCN_EPI_MASK && (!d_mask || ldmask < w)) return fail(GCN_E_INVALID, "gcn_aggregate: mask missing");
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, graph_aggregate_workspace(g, w, ldm), "gcn_aggregate", &query));
+  const size_t need = graph_aggregate_workspace(g, w, ldm, true);
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, need, "gcn_aggregate", &query, graph_aggregate_workspace(g, w, ldm, false)));
   if (query) return GCN_OK;
   if (g->n > 0 && w > 0 && (!d_M || !d_Z)) return fail(GCN_E_INVALID, "gcn_aggregate: d_M and d_Z are required");
-  AggParams p = graph_agg(g, w, d_M, ldm, d_Z, ldz, agg);
+  AggParams p = graph_agg(g, w, d_M, ldm, d_Z, ldz, agg, *ws_bytes >= need);
   p.bias = d_bias;
   p.epi = epi == GCN_EPI_RELU ? AGG_RELU : (epi == GCN_EPI_MASK ? AGG_MASK : AGG_NONE);
   p.mask = d_mask;
@@ -697,7 +716,7 @@ gcn_status gcn_aggregate_max(const gcn_graph* g, int32_t w, const float* d_M, in
   GCN_TRY(ws_protocol(d_ws, ws_bytes, 0, "gcn_aggregate_max", &query));
   if (query) return GCN_OK;
   if (g->n > 0 && w > 0 && (!d_M || !d_P || !d_arg)) return fail(GCN_E_INVALID, "gcn_aggregate_max: NULL buffer");
-  return launch_aggregate_max(graph_agg(g, w, d_M, ldm, d_P, ldp), g->nnz, d_P, ldp, d_arg, ldarg, stream);
+  return launch_aggregate_max(graph_agg(g, w, d_M, ldm, d_P, ldp, GCN_AGG_MAX, false), g->nnz, d_P, ldp, d_arg, ldarg, stream);
 }
 
 gcn_status gcn_aggregate_max_bwd(const gcn_graph* g, int32_t w, const float* d_dP, int64_t ldd,
@@ -713,7 +732,7 @@ gcn_status gcn_aggregate_max_bwd(const gcn_graph* g, int32_t w, const float* d_d
   if (query) return GCN_OK;
   if (g->n > 0 && w > 0 && (!d_dP || !d_arg || !d_dM))
     return fail(GCN_E_INVALID, "gcn_aggregate_max_bwd: NULL buffer");
-  return launch_aggregate_max_bwd(graph_agg(g, w, d_dP, ldd, d_dM, ldo), g->nnz, d_arg, ldarg, d_mask, ldmask,
+  return launch_aggregate_max_bwd(graph_agg(g, w, d_dP, ldd, d_dM, ldo, GCN_AGG_MAX, false), g->nnz, d_arg, ldarg, d_mask, ldmask,
                                   d_dM, ldo, stream);
 }
 

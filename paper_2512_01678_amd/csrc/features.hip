@@ -39,27 +39,27 @@ struct FeatWs {
   int32_t* row_cnt;    // n
   int64_t* row_off;    // n + 1 (used when the caller supplies no CSR buffer)
   void* scan;
-  uint32_t* bits;      // n * words: 1[x != 0], 32 columns per word
-  int64_t words;
   int32_t* chunk_cnt;  // nchunks * f
   int32_t* chunk_off;  // nchunks * f
   int32_t* col_tot;    // f
   int64_t nchunks;
   void* split;         // split plan scratch for long CSC columns
+  uint32_t* bits;      // n * words: 1[x != 0], 32 columns per word (last: a workspace may end before it)
+  int64_t words;
 };
 
-FeatWs carve(Arena& a, int32_t n, int32_t f, bool views, bool csc) {
+FeatWs carve(Arena& a, int32_t n, int32_t f, bool bits, bool csc) {
   FeatWs w;
   w.row_cnt = a.take<int32_t>(n);
   w.row_off = a.take<int64_t>((int64_t)n + 1);
   w.scan = a.take<char>((int64_t)scan_workspace(std::max<int64_t>(n, f) + 1));
-  w.words = ceil_div(f, 32);
-  w.bits = a.take<uint32_t>(views ? n * w.words : 0);
   w.nchunks = ceil_div(n, chunk_rows(n, f));
   w.chunk_cnt = a.take<int32_t>(csc ? w.nchunks * f : 0);
   w.chunk_off = a.take<int32_t>(csc ? w.nchunks * f : 0);
   w.col_tot = a.take<int32_t>(csc ? f : 0);
   w.split = a.take<char>(csc ? (int64_t)split_workspace(f) : 0);
+  w.words = ceil_div(f, 32);
+  w.bits = bits ? a.take<uint32_t>(n * w.words) : nullptr;
   return w;
 }
 
@@ -300,20 +300,20 @@ __global__ void __launch_bounds__(64) k_to_csc(const int64_t* row_ptr, const int
 
 }  // namespace
 
-size_t feature_stats_workspace(int32_t n, int32_t f, bool views, bool want_csc) {
+size_t feature_stats_workspace(int32_t n, int32_t f, bool bits, bool want_csc) {
   Arena a;
-  carve(a, n, f, views, want_csc);
+  carve(a, n, f, bits, want_csc);
   return a.used;
 }
 
 gcn_status run_feature_stats(const float* X, int32_t n, int32_t f, int64_t ldx, int32_t tau_num,
-                             int32_t tau_den, int32_t force_mode, int64_t* row_nnz,
-                             gcn_feature_info* info, gcn_sparse_x* x, void* ws, hipStream_t s) {
+                             int32_t tau_den, int32_t force_mode, int64_t* row_nnz, gcn_feature_info* info,
+                             gcn_sparse_x* x, bool have_bits, void* ws, hipStream_t s) {
   const bool want_csc = x && x->col_ptr;
   Arena a;
   a.base = static_cast<char*>(ws);
-  FeatWs w = carve(a, n, f, x != nullptr, want_csc);
-  uint32_t* const bits = x ? w.bits : nullptr;
+  FeatWs w = carve(a, n, f, have_bits, want_csc);
+  uint32_t* const bits = w.bits;
   if (n > 0) {
     // a grid that fills the chip twice over: a wavefront walks many rows
     const unsigned gw = (unsigned)std::min<int64_t>(ceil_div(n, 4), 4096);
@@ -345,7 +345,7 @@ gcn_status run_feature_stats(const float* X, int32_t n, int32_t f, int64_t ldx, 
     // From one nonzero in 20 on, most lines of X hold one: read it again in order (262,144 x
     // 1,024, whole call: 3 % 629 us from the bits, 685 by the walk; 6 % 723 and 706; 50 % 4,234
     // and 903).
-    if ((__int128)nnz * 20 >= nf) {
+    if (!bits || (__int128)nnz * 20 >= nf) {
       hipLaunchKernelGGL(k_to_csr, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, s, X, n, f, ldx, x->row_ptr, x->col,
                          x->val);
     } else {

@@ -44,6 +44,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 struct Arena {
   char* base = nullptr;  // NULL while measuring
   size_t used = 0;
+  bool lean = false;     // without the room that only makes a call faster (row pieces)
   template <class T>
   T* take(int64_t count) {
     used = (size_t)round_up((int64_t)used, 256);
@@ -119,8 +120,9 @@ gcn_status launch_agg_blocked(const AggParams& p, const BlockedPlan& b, const gc
 // Z over all rows; rows longer than GCN_SPLIT_MIN go through the split plan when one
 // is given (its chunk sums live in ws, aggregate_workspace() bytes).
 size_t aggregate_workspace(const gcn_split* split, int32_t w);
-// The same for a graph of n nodes whose aggregations may be blocked (ldm: pitch of M).
-size_t graph_aggregate_workspace(const gcn_graph* g, int32_t w, int64_t ldm);
+// The same for a graph of n nodes, and for the row pieces if its aggregations may be blocked
+// (ldm: pitch of M).
+size_t graph_aggregate_workspace(const gcn_graph* g, int32_t w, int64_t ldm, bool may_block);
 gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* split, void* ws,
                             hipStream_t s);
 inline bool has_split(const gcn_split* sp) { return sp && sp->rows && sp->n_long > 0; }
@@ -239,11 +241,12 @@ size_t build_csr_workspace(int32_t n, int64_t n_edges);
 gcn_status run_build_csr(int32_t n, int64_t n_edges, const int32_t* src, const int32_t* dst,
                          gcn_graph* g, void* ws, hipStream_t s);
 
-// views: X_csr is wanted too; want_csc: and X_csc.
-size_t feature_stats_workspace(int32_t n, int32_t f, bool views, bool want_csc);
+// bits: with room for one bit per element of X (the views from it cost one read of X less);
+// want_csc: X_csc is wanted too.
+size_t feature_stats_workspace(int32_t n, int32_t f, bool bits, bool want_csc);
 gcn_status run_feature_stats(const float* X, int32_t n, int32_t f, int64_t ldx, int32_t tau_num,
-                             int32_t tau_den, int32_t force_mode, int64_t* row_nnz,
-                             gcn_feature_info* info, gcn_sparse_x* x, void* ws, hipStream_t s);
+                             int32_t tau_den, int32_t force_mode, int64_t* row_nnz, gcn_feature_info* info,
+                             gcn_sparse_x* x, bool have_bits, void* ws, hipStream_t s);
 
 // step >= 1 from the host, or (d_step != NULL) read from and incremented on the device
 gcn_status launch_adam(const gcn_adam_tensor* t, int32_t count, int32_t step, int32_t* d_step, double lr,

@@ -1074,3 +1074,108 @@ def test_build_csr_all_pairs_in_one_sub_bucket(G):
     assert host(g.row_ptr[:4]).tolist() == [0, 2, 4, 5] and int(g.row_ptr[n]) == n + 2
     want = np.float32(1 / np.sqrt(2))
     np.testing.assert_array_equal(host(g.val)[:5], np.array([want * want] * 4 + [1.0], np.float32))
+
+
+def call_sized(G, fn, before, st, nbytes):
+    buf = torch.full((max(nbytes, 256),), 0xEE, dtype=torch.uint8, device="cuda")
+    rc = fn(*before, buf.data_ptr(), C.byref(G.sz(nbytes)), st)
+    torch.cuda.synchronize()
+    return rc
+
+
+@pytest.mark.parametrize("split", [True, False])
+def test_aggregate_with_the_chunk_sums_alone(G, orc, split):
+    """gcn_aggregate takes a workspace that holds the chunk sums of the split rows and no more: the
+    sums of a dense graph are then not blocked by source rows.  One byte less is refused."""
+    n, w = 30000, 64
+    s, d = gs.chung_lu(n, 1100000, seed=3, dmax=6000.0)
+    og, dg = orc.build_csr(n, s, d), G.build_csr(n, dev(s), dev(d), split=split)
+    assert (dg.n_long > 0) == split
+    rng = np.random.default_rng(1)
+    M = rng.standard_normal((n, w)).astype(np.float32)
+    Md, Z = dev(M), torch.full((n, w), float("nan"), device="cuda")
+    L, st = G.raw_lib(), C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    before = (C.byref(dg.c), G.AGG_NORM, w, Md.data_ptr(), w, None, G.EPI_NONE, None, 0, Z.data_ptr(), w)
+    least = 4 * w * dg.c.split.n_chunk if split else 0
+    full = G.sz(0)
+    assert L.gcn_aggregate(*before, None, C.byref(full), st) == G.OK and full.value > least
+    rows = rng.integers(0, n, 200)
+    want, mag = orc.aggregate(og, M, rows=rows, want_mag=True)
+    for nbytes in (least, full.value - 1, full.value):
+        Z.fill_(float("nan"))
+        assert call_sized(G, L.gcn_aggregate, before, st, nbytes) == G.OK, L.gcn_last_error()
+        assert_mag_close(host(Z)[rows], want, mag, f"workspace of {nbytes}")
+    if least:
+        assert call_sized(G, L.gcn_aggregate, before, st, least - 1) == G.E_CAPACITY
+
+
+def test_layers_with_a_workspace_sized_before_the_graph_was_built(G, orc):
+    """A layer's or an epoch's workspace may be sized before the entries of a graph (without a split
+    plan) are known; the call takes it."""
+    n, fi, fo = 30000, 64, 41
+    s, d = gs.chung_lu(n, 1100000, seed=3, dmax=6000.0)
+    dg = G.build_csr(n, dev(s), dev(d), split=False)
+    rng = np.random.default_rng(1)
+    H, W, b = rng.standard_normal((n, fi)), rng.standard_normal((fi, fo)) / 8, rng.standard_normal(fo)
+    Hd, Wd, bd = dev(H.astype(np.float32)), dev(W.astype(np.float32)), dev(b.astype(np.float32))
+    unbuilt = G.gcn_graph(n, 0, dg.c.nnz_cap, dg.c.row_ptr, dg.c.col_idx, dg.c.deg, dg.c.dinv, dg.c.val)
+    Ly = G.make_layer(fi, fo, fi, G.pitch(fo), G.ACT_RELU, 1)
+    out, st = G.padded(n, fo), C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    L = G.raw_lib()
+    fwd = (C.byref(Ly), Hd.data_ptr(), None, Wd.data_ptr(), bd.data_ptr(), out.data_ptr(), None, None, None, None)
+    early, full = G.sz(0), G.sz(0)
+    assert L.gcn_layer_fwd(C.byref(unbuilt), *fwd, None, C.byref(early), st) == G.OK
+    assert L.gcn_layer_fwd(C.byref(dg.c), *fwd, None, C.byref(full), st) == G.OK and full.value > early.value
+    assert call_sized(G, L.gcn_layer_fwd, (C.byref(dg.c), *fwd), st, early.value) == G.OK, L.gcn_last_error()
+    got = host(out).copy()
+    G.layer_fwd(dg, Ly, Hd, None, Wd, bd, out)
+    assert_norm_close(got, host(out), "forward, the smaller workspace", 1e-5)
+    assert call_sized(G, L.gcn_layer_fwd, (C.byref(dg.c), *fwd), st, early.value - 1) == G.E_CAPACITY
+    Gr = dev((rng.standard_normal((n, G.pitch(fo))) / n).astype(np.float32))
+    dW, db, Gp = torch.zeros_like(Wd), torch.zeros_like(bd), torch.zeros((n, fi), device="cuda")
+    bwd = (C.byref(Ly), Gr.data_ptr(), Hd.data_ptr(), None, None, Wd.data_ptr(), dW.data_ptr(), db.data_ptr(), Gp.data_ptr())
+    assert L.gcn_layer_bwd(C.byref(unbuilt), *bwd, None, C.byref(early), st) == G.OK
+    assert call_sized(G, L.gcn_layer_bwd, (C.byref(dg.c), *bwd), st, early.value) == G.OK, L.gcn_last_error()
+    small = [host(t).copy() for t in (dW, db, Gp)]
+    G.layer_bwd(dg, Ly, Gr[:, :fo], Hd, None, None, Wd, dW, db, Gp)
+    for a, t in zip(small, (dW, db, Gp)):
+        assert_norm_close(a, host(t), "backward, the smaller workspace", 1e-5)
+    y = dev(rng.integers(0, fo, n).astype(np.int32))
+    losses = []
+    for g in (unbuilt, dg.c):
+        m = G.Model(n, (fi, fo), [W], [b], ld_x=fi)
+        arg = (C.byref(m.c), C.byref(dg.c), Hd.data_ptr(), None, y.data_ptr(), m.loss.data_ptr())
+        assert L.gcn_epoch(arg[0], C.byref(g), *arg[2:], None, C.byref(early), st) == G.OK
+        assert call_sized(G, L.gcn_epoch, arg, st, early.value) == G.OK, L.gcn_last_error()
+        losses.append((float(m.loss), host(m.dW[0])))
+    assert losses[0][0] == pytest.approx(losses[1][0], rel=1e-5)
+    assert_norm_close(losses[0][1], losses[1][1], "epoch, the smaller workspace", 1e-5)
+
+
+@pytest.mark.parametrize("csc", [False, True])
+def test_feature_views_with_the_counting_workspace(G, orc, csc):
+    """The views come out of a workspace without room for the bits of X too (the size that a query
+    without the CSR view gives)."""
+    n, f = 500, 300
+    rng = np.random.default_rng(4)
+    X = np.where(rng.random((n, f)) < 0.02, rng.standard_normal((n, f)), 0.0).astype(np.float32)
+    Xd, nnz = dev(X), int((X != 0).sum())
+    sx, info = G.SparseFeatures(n, f, nnz, "cuda", csc=csc), G.gcn_feature_info()
+    L, st = G.raw_lib(), C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    head = (Xd.data_ptr(), n, f, f, 4, 5, -1, None, C.byref(info))
+    least, full = G.sz(0), G.sz(0)
+    assert L.gcn_feature_stats(*head, C.byref(sx.c), None, C.byref(full), st) == G.OK
+    if csc:
+        least.value = full.value - 4 * n * ((f + 31) // 32)
+    else:
+        assert L.gcn_feature_stats(*head, None, None, C.byref(least), st) == G.OK
+    assert least.value < full.value
+    for nbytes in (least.value, full.value):
+        sx.c.nnz = nnz
+        assert call_sized(G, L.gcn_feature_stats, (*head, C.byref(sx.c)), st, nbytes) == G.OK, L.gcn_last_error()
+        rp, col, val = orc.dense_to_csr(X)
+        np.testing.assert_array_equal(host(sx.row_ptr), rp)
+        np.testing.assert_array_equal(host(sx.col)[:nnz], col)
+        np.testing.assert_array_equal(host(sx.val)[:nnz], val.astype(np.float32))
+        if csc:
+            np.testing.assert_array_equal(host(sx.row)[:nnz], orc.dense_to_csc(X)[1])
