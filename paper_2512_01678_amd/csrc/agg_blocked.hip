@@ -167,9 +167,9 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
 
   // Lane 4 r + q holds the piece of round r, wavefront q: every wavefront knows all of them.
   const bool chunks = (int)blockIdx.x < lr.groups;
-  const int64_t nwaves = (int64_t)((int)gridDim.x - lr.groups) * kWalkWaves;
-  const int64_t hi = (int64_t)((int)blockIdx.x - (chunks ? 0 : lr.groups)) * kWalkWaves + L.lig % kWalkWaves +
-                     (int64_t)(L.lig / kWalkWaves) * nwaves;
+  const int64_t ngroups = (int)gridDim.x - lr.groups;
+  const int64_t group = chunks ? (int64_t)blockIdx.x : walk_group((int)blockIdx.x - lr.groups, ngroups);
+  const int64_t hi = group * kWalkWaves + L.lig % kWalkWaves + (int64_t)(L.lig / kWalkWaves) * ngroups * kWalkWaves;
   Piece h{0, 0, -1};
   if (chunks) {
     rounds = 1;

@@ -1179,3 +1179,26 @@ def test_feature_views_with_the_counting_workspace(G, orc, csc):
         np.testing.assert_array_equal(host(sx.val)[:nnz], val.astype(np.float32))
         if csc:
             np.testing.assert_array_equal(host(sx.row)[:nnz], orc.dense_to_csc(X)[1])
+
+
+@pytest.mark.parametrize("n", [1, 2, 4, 5, 31, 32, 33, 64, 65, 96, 127, 129, 255, 257, 1000])
+def test_every_row_is_walked_once(G, orc, n):
+    """Workgroups of four rows take their places turned within each eight of them: every row comes
+    out, whatever is left over at the end of the eights."""
+    rng = np.random.default_rng(n)
+    s, d = messy(rng, n, 5 * n)
+    og, dg = orc.build_csr(n, s, d), G.build_csr(n, dev(s), dev(d))
+    M = rng.standard_normal((n, 40)).astype(np.float32)
+    Z = torch.full((n, 40), float("nan"), device="cuda")
+    G.aggregate(dg, dev(M), Z)
+    want, mag = orc.aggregate(og, M, want_mag=True)
+    assert_mag_close(host(Z), want, mag, f"{n} rows")
+    P, arg = orc.aggregate_max(og, M)
+    Z.fill_(float("nan"))
+    argd = torch.full((n, 40), -7, dtype=torch.int32, device="cuda")
+    G.aggregate_max(dg, dev(M), Z, argd)
+    np.testing.assert_array_equal(host(Z), P.astype(np.float32))
+    np.testing.assert_array_equal(host(argd), arg)
+    Z.fill_(float("nan"))
+    G.aggregate_max_bwd(dg, dev(M), argd, Z)
+    assert_mag_close(host(Z), orc.aggregate_max_backward(og, M, arg), orc.aggregate_max_backward(og, np.abs(M), arg), f"{n} rows, gradient")
