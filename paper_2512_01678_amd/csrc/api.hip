@@ -27,10 +27,8 @@ gcn_status hip_fail(hipError_t e, const char* what) {
 
 namespace {
 
-// Workspace protocol: NULL buffer -> report size; else check it is large enough.  A call that
-// can do with less room than it reports (`least`) runs in that too.
-gcn_status ws_protocol(void* d_ws, size_t* ws_bytes, size_t need, const char* who, bool* query,
-                       size_t least = SIZE_MAX) {
+// Workspace protocol: NULL buffer -> report size; else check it is large enough.
+gcn_status ws_protocol(void* d_ws, size_t* ws_bytes, size_t need, const char* who, bool* query) {
   if (!ws_bytes) return fail(GCN_E_INVALID, std::string(who) + ": ws_bytes is NULL");
   if (!d_ws) {
     *ws_bytes = need;
@@ -38,12 +36,15 @@ gcn_status ws_protocol(void* d_ws, size_t* ws_bytes, size_t need, const char* wh
     return GCN_OK;
   }
   *query = false;
-  need = std::min(need, least);
   if (*ws_bytes < need)
     return fail(GCN_E_CAPACITY, std::string(who) + ": workspace of " + std::to_string(*ws_bytes) +
                                     " bytes, " + std::to_string(need) + " needed");
   return GCN_OK;
 }
+
+// Whether a call is given a workspace of less than `need` bytes: it then plans again with lean
+// arenas, and ws_protocol decides about that.
+bool short_of(void* d_ws, const size_t* ws_bytes, size_t need) { return d_ws && ws_bytes && *ws_bytes < need; }
 
 gcn_status check_graph(const gcn_graph* g, const char* who) {
   if (!g) return fail(GCN_E_INVALID, std::string(who) + ": graph is NULL");
@@ -496,16 +497,17 @@ gcn_status gcn_feature_stats(const float* d_X, int32_t n, int32_t f, int64_t ldx
   if (force_mode < -1 || force_mode > GCN_SPARSE) return fail(GCN_E_INVALID, "gcn_feature_stats: bad force_mode");
   const bool csc = x && x->col_ptr;
   bool query = false;
-  const size_t need = feature_stats_workspace(n, f, x != nullptr, csc);
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, need, "gcn_feature_stats", &query, feature_stats_workspace(n, f, false, csc)));
+  size_t need = feature_stats_workspace(n, f, x != nullptr, csc);
+  const bool lean = short_of(d_ws, ws_bytes, need);
+  if (lean) need = feature_stats_workspace(n, f, false, csc);
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, need, "gcn_feature_stats", &query));
   if (query) return GCN_OK;
   if (!info || (n > 0 && f > 0 && !d_X)) return fail(GCN_E_INVALID, "gcn_feature_stats: X and info are required");
   if (x && (!x->row_ptr || !x->col || !x->val || (csc && (!x->row || !x->cval))))
     return fail(GCN_E_INVALID, "gcn_feature_stats: sparse output arrays missing");
   if (x && csc && x->csc_split.rows && (!x->csc_split.first || !x->csc_split.owner || x->csc_split.cap < 0))
     return fail(GCN_E_INVALID, "gcn_feature_stats: split plan arrays missing");
-  return run_feature_stats(d_X, n, f, ldx, tau_num, tau_den, force_mode, d_row_nnz, info, x, x && *ws_bytes >= need, d_ws,
-                           stream);
+  return run_feature_stats(d_X, n, f, ldx, tau_num, tau_den, force_mode, d_row_nnz, info, x, x && !lean, d_ws, stream);
 }
 
 gcn_status gcn_layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* d_Hin,
@@ -514,16 +516,19 @@ gcn_status gcn_layer_fwd(const gcn_graph* g, const gcn_layer* L, const float* d_
                          void* d_ws, size_t* ws_bytes, hipStream_t stream) {
   g_err.clear();
   GCN_TRY(validate_fwd(g, L, d_Hin, x, d_W, d_Hout, d_saved, d_labels, d_loss, "gcn_layer_fwd"));
-  Arena plan, least;
-  least.lean = true;
+  Arena plan;
   GCN_TRY(layer_fwd(g, L, d_Hin, x, d_W, d_b, d_Hout, d_saved, d_labels, d_loss, d_logits, plan, stream));
-  GCN_TRY(layer_fwd(g, L, d_Hin, x, d_W, d_b, d_Hout, d_saved, d_labels, d_loss, d_logits, least, stream));
+  if (short_of(d_ws, ws_bytes, plan.used)) {
+    plan = Arena{};
+    plan.lean = true;
+    GCN_TRY(layer_fwd(g, L, d_Hin, x, d_W, d_b, d_Hout, d_saved, d_labels, d_loss, d_logits, plan, stream));
+  }
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, plan.used, "gcn_layer_fwd", &query, least.used));
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, plan.used, "gcn_layer_fwd", &query));
   if (query) return GCN_OK;
   Arena a;
   a.base = static_cast<char*>(d_ws);
-  a.lean = *ws_bytes < plan.used;
+  a.lean = plan.lean;
   return layer_fwd(g, L, d_Hin, x, d_W, d_b, d_Hout, d_saved, d_labels, d_loss, d_logits, a, stream);
 }
 
@@ -532,16 +537,19 @@ gcn_status gcn_layer_bwd(const gcn_graph* g, const gcn_layer* L, const float* d_
                          float* d_db, float* d_Gprev, void* d_ws, size_t* ws_bytes, hipStream_t stream) {
   g_err.clear();
   GCN_TRY(validate_bwd(g, L, d_G, d_Hin, x, d_saved, d_W, d_dW, d_db, d_Gprev, "gcn_layer_bwd"));
-  Arena plan, least;
-  least.lean = true;
+  Arena plan;
   GCN_TRY(layer_bwd(g, L, d_G, d_Hin, x, d_saved, d_W, d_dW, d_db, d_Gprev, plan, stream));
-  GCN_TRY(layer_bwd(g, L, d_G, d_Hin, x, d_saved, d_W, d_dW, d_db, d_Gprev, least, stream));
+  if (short_of(d_ws, ws_bytes, plan.used)) {
+    plan = Arena{};
+    plan.lean = true;
+    GCN_TRY(layer_bwd(g, L, d_G, d_Hin, x, d_saved, d_W, d_dW, d_db, d_Gprev, plan, stream));
+  }
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, plan.used, "gcn_layer_bwd", &query, least.used));
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, plan.used, "gcn_layer_bwd", &query));
   if (query) return GCN_OK;
   Arena a;
   a.base = static_cast<char*>(d_ws);
-  a.lean = *ws_bytes < plan.used;
+  a.lean = plan.lean;
   return layer_bwd(g, L, d_G, d_Hin, x, d_saved, d_W, d_dW, d_db, d_Gprev, a, stream);
 }
 
@@ -578,17 +586,18 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
   uint32_t* const probe = reinterpret_cast<uint32_t*>((uintptr_t)256);
   float* const probe_db = reinterpret_cast<float*>((uintptr_t)256);
   bool writes[8] = {}, reads[8] = {}, sums[8] = {};  // sums[l]: layer l's backward can write db[l-1]
-  size_t need = 0, least = 0;  // least: with lean arenas
-  for (int l = 0; l < L; ++l) {
-    const gcn_layer* ly = &m->layers[l];
-    const float* Hin = l == 0 ? d_X : m->act[l - 1];
-    const gcn_sparse_x* xl = l == 0 ? x : nullptr;
-    float* Hout = l < L - 1 ? m->act[l] : m->grad[l];
-    float* saved = m->saved ? m->saved[l] : nullptr;
-    GCN_TRY(validate_fwd(g, ly, Hin, xl, m->W[l], Hout, saved, d_labels, d_loss, who));
-    GCN_TRY(validate_bwd(g, ly, m->grad[l], Hin, xl, saved, m->W[l], m->dW[l], m->db[l],
-                         l > 0 ? m->grad[l - 1] : nullptr, who));
-    for (const bool lean : {false, true}) {
+  size_t need = 0;
+  auto plan = [&](bool lean) -> gcn_status {
+    need = 0;
+    for (int l = 0; l < L; ++l) {
+      const gcn_layer* ly = &m->layers[l];
+      const float* Hin = l == 0 ? d_X : m->act[l - 1];
+      const gcn_sparse_x* xl = l == 0 ? x : nullptr;
+      float* Hout = l < L - 1 ? m->act[l] : m->grad[l];
+      float* saved = m->saved ? m->saved[l] : nullptr;
+      GCN_TRY(validate_fwd(g, ly, Hin, xl, m->W[l], Hout, saved, d_labels, d_loss, who));
+      GCN_TRY(validate_bwd(g, ly, m->grad[l], Hin, xl, saved, m->W[l], m->dW[l], m->db[l],
+                           l > 0 ? m->grad[l - 1] : nullptr, who));
       Arena pf, pb;
       pf.lean = pb.lean = lean;
       GCN_TRY(layer_fwd(g, ly, Hin, xl, m->W[l], m->b[l], Hout, saved, d_labels, d_loss, nullptr, pf, stream,
@@ -596,10 +605,11 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
       GCN_TRY(layer_bwd(g, ly, m->grad[l], Hin, xl, saved, m->W[l], m->dW[l], m->db[l],
                         l > 0 ? m->grad[l - 1] : nullptr, pb, stream, l > 0 ? probe : nullptr, &reads[l],
                         l > 0 ? probe_db : nullptr, &sums[l]));
-      size_t& most = lean ? least : need;
-      most = std::max(most, std::max(pf.used, pb.used));
+      need = std::max(need, std::max(pf.used, pb.used));
     }
-  }
+    return GCN_OK;
+  };
+  GCN_TRY(plan(false));
   int64_t bits_at[8];
   size_t bits_bytes = 0;
   for (int l = 0; l < L; ++l) {
@@ -637,9 +647,10 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
     }
   }
   bool query = false;
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, bits_bytes + need, who, &query, bits_bytes + least));
+  const bool lean = short_of(d_ws, ws_bytes, bits_bytes + need);
+  if (lean) GCN_TRY(plan(true));
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, bits_bytes + need, who, &query));
   if (query) return GCN_OK;
-  const bool lean = *ws_bytes < bits_bytes + need;
   char* const base = static_cast<char*>(d_ws);
   auto bits_of = [&](int l) { return bits_at[l] < 0 ? nullptr : reinterpret_cast<uint32_t*>(base + bits_at[l]); };
   for (int q = 0; q < njobs; ++q) jobs[q].out = base + job_at[q];
@@ -693,11 +704,13 @@ gcn_status gcn_aggregate(const gcn_graph* g, int32_t agg, int32_t w, const float
   if (epi < GCN_EPI_NONE || epi > GCN_EPI_MASK) return fail(GCN_E_INVALID, "gcn_aggregate: unknown epilogue");
   if (epi == GCN_EPI_MASK && (!d_mask || ldmask < w)) return fail(GCN_E_INVALID, "gcn_aggregate: mask missing");
   bool query = false;
-  const size_t need = graph_aggregate_workspace(g, w, ldm, true);
-  GCN_TRY(ws_protocol(d_ws, ws_bytes, need, "gcn_aggregate", &query, graph_aggregate_workspace(g, w, ldm, false)));
+  size_t need = graph_aggregate_workspace(g, w, ldm, true);
+  const bool lean = short_of(d_ws, ws_bytes, need);
+  if (lean) need = graph_aggregate_workspace(g, w, ldm, false);
+  GCN_TRY(ws_protocol(d_ws, ws_bytes, need, "gcn_aggregate", &query));
   if (query) return GCN_OK;
   if (g->n > 0 && w > 0 && (!d_M || !d_Z)) return fail(GCN_E_INVALID, "gcn_aggregate: d_M and d_Z are required");
-  AggParams p = graph_agg(g, w, d_M, ldm, d_Z, ldz, agg, *ws_bytes >= need);
+  AggParams p = graph_agg(g, w, d_M, ldm, d_Z, ldz, agg, !lean);
   p.bias = d_bias;
   p.epi = epi == GCN_EPI_RELU ? AGG_RELU : (epi == GCN_EPI_MASK ? AGG_MASK : AGG_NONE);
   p.mask = d_mask;
