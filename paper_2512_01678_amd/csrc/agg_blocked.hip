@@ -22,7 +22,9 @@
 // panel, so that a line is fetched into each L2 once and most further gathers of it hit there.
 // The entries of a row that fall into a block are a contiguous piece of it, found by binary
 // search at the start of the call.  Between the launches a row's partial sum rests in Z; the
-// last launch applies the epilogue.  Every sum has a fixed order: deterministic.
+// last launch applies the epilogue.  The others leave a row alone that they have no entry of
+// (with local ids a row's entries lie in one block or two: 232,965 rows joined to the 490 around
+// them, width 256, 6,452 -> 5,197 us).  Every sum has a fixed order: deterministic.
 //
 // Measured (us, before -> now, the same box): 232,965 rows of 484 entries, width 256 13,700 ->
 // 7,390, width 41 3,050 -> 1,930; 169,343 rows of 15, width 256 342 -> 306, 128 170 -> 157, 40
@@ -150,9 +152,13 @@ __device__ __forceinline__ void store_row(const AggParams& p, int64_t row, float
   }
 }
 
+// In a blocked launch a piece's row carries whether earlier blocks left a partial sum of the row
+// (rows stay below 2^26: M is below 4 GB and more than 16 columns wide).
+constexpr int32_t kGoesOn = 1 << 30;
+
 // Workgroup b's wavefront w sums the pieces of rows 4 b + w, 4 b + w + nwaves, ... (`rounds` of
 // them; in processing order when blocked, so that rows of like length run together).
-template <int LANES, int EPI>
+template <int LANES, int EPI, bool BLOCKED>
 __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const Piece* pieces, int32_t block,
                                                                int32_t nblock, int32_t rounds, LongRows lr) {
   constexpr int SL = 64 / LANES;
@@ -163,7 +169,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
   const char* Mc = reinterpret_cast<const char*>(p.M);
   const uint32_t lane_off = cok ? 4u * (uint32_t)L.c0 : 0u;  // lanes past the width re-read column 0 (not used)
   const uint32_t pitch = 4u * (uint32_t)p.ldm;
-  const bool first = block == 0, last = block == nblock - 1;
+  const bool last = block == nblock - 1;
 
   // Lane 4 r + q holds the piece of round r, wavefront q: every wavefront knows all of them.
   const bool chunks = (int)blockIdx.x < lr.groups;
@@ -182,7 +188,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
       h.row = (int)ch;
     }
   } else if (L.lig < kWalkWaves * rounds && hi < p.n) {
-    if (nblock > 1) {
+    if (BLOCKED) {
       h = pieces[(int64_t)block * p.n + hi];
     } else {
       const int64_t beg = p.row_ptr[hi], end = p.row_ptr[hi + 1];
@@ -200,7 +206,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
     if (L.c0 + 2 < p.w) bias.z = p.bias[L.c0 + 2];
     if (L.c0 + 3 < p.w) bias.w = p.bias[L.c0 + 3];
   }
-  const float h_scale = EPI != AGG_SOFTMAX && last && !chunks && items.row >= 0 ? row_scale(p, items.row) : 1.f;
+  const float h_scale = EPI != AGG_SOFTMAX && last && !chunks && items.row >= 0 ? row_scale(p, BLOCKED ? items.row & ~kGoesOn : items.row) : 1.f;
 
   // The entries are requested two chunks ahead of the gathers: a chunk's indices come from
   // behind the L2, its gathers mostly from it.
@@ -230,15 +236,16 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
   };
   int parity = 0;
   for (int t = 0; t < items.n; ++t) {
-    const int row = __builtin_amdgcn_readlane(items.row, t);
+    const int tagged = __builtin_amdgcn_readlane(items.row, t);
     const int len = __builtin_amdgcn_readlane(items.len, t);
     const int fin = __builtin_amdgcn_readlane(items.kind, t);
+    const int row = BLOCKED && tagged >= 0 ? tagged & ~kGoesOn : tagged;
     const bool mine = row >= 0 && (fin < 0 || fin == wave);
     float* z = (chunks ? lr.part + row * lr.pw : p.Z + (int64_t)(row < 0 ? 0 : row) * p.ldz) + L.c0;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float4 part = acc, mk = acc;
     // (the loss epilogue keeps a row's sum in any slice, the others in slice 0)
-    if (!first && cok && (EPI == AGG_SOFTMAX || L.slot == 0) && mine) part = *reinterpret_cast<const float4*>(z);
+    if (BLOCKED && (tagged & kGoesOn) && cok && (EPI == AGG_SOFTMAX || L.slot == 0) && mine) part = *reinterpret_cast<const float4*>(z);
     if (EPI == AGG_MASK && last && !chunks && cok && L.slot == 0 && mine)
       mk = *reinterpret_cast<const float4*>(p.mask + (int64_t)row * p.ldmask + L.c0);
     int done = 0;
@@ -319,30 +326,46 @@ __global__ void __launch_bounds__(kWalkThreads) k_finish_long(AggParams p, LongR
 }
 
 // pieces[b * n + i]: the entries of the i-th row in processing order whose source rows lie in
-// block b.  Each search starts at the end before it, so the pieces make up the row whatever the
+// block b.  A group of G lanes per row, a lane per block: each finds the end of its block by binary
+// search, and the running maximum over the lanes makes the pieces make up the row whatever the
 // order of its columns; ascending ones (gcn_build_csr) make each block's gathers stay in it.
+// (Bound by the latency of the searches: one thread per row, block after block, took 202 us for
+// 232,965 rows and ten blocks, 70 now.)
+template <int G>
 __global__ void __launch_bounds__(256) k_block_pieces(int32_t n, const int64_t* row_ptr, const int32_t* col,
                                                       const int32_t* order, int32_t rows, int32_t nblock,
                                                       Piece* pieces) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
+  const int lane = threadIdx.x % G;
+  if (i >= n) return;  // whole groups leave together
   const int32_t row = order ? order[i] : (int32_t)i;
-  const int64_t end = row_ptr[row + 1];
-  int64_t lo = row_ptr[row];
-  for (int32_t b = 0; b < nblock; ++b) {
-    const int64_t beg = lo;
-    int64_t hi = end;
+  const int64_t beg = row_ptr[row];
+  const int32_t len = (int32_t)(row_ptr[row + 1] - beg);
+  const int32_t* const c = col + beg;
+  int32_t from = 0;  // where the blocks of this turn start
+  for (int32_t b0 = 0; b0 < nblock; b0 += G) {
+    const int32_t b = b0 + lane;
+    int32_t at = len;
     if (b + 1 < nblock) {
       const int64_t bound = (int64_t)(b + 1) * rows;
-      while (lo < hi) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (col[mid] < bound) lo = mid + 1;
-        else hi = mid;
+      int32_t lo = from;
+      while (lo < at) {
+        const int32_t mid = lo + (at - lo) / 2;
+        if (c[mid] < bound) lo = mid + 1;
+        else at = mid;
       }
-    } else {
-      lo = end;
     }
-    pieces[(int64_t)b * n + i] = Piece{beg, (int32_t)(lo - beg), row};
+    for (int o = 1; o < G; o <<= 1) {
+      const int32_t before = __shfl_up(at, o, G);
+      if (lane >= o && before > at) at = before;
+    }
+    int32_t start = __shfl_up(at, 1, G);
+    if (lane == 0) start = from;
+    if (b < nblock) {
+      const bool idle = at == start && b + 1 < nblock;  // no entry here: nothing to do before the end
+      pieces[(int64_t)b * n + i] = Piece{beg + start, at - start, idle ? -1 : row | (start > 0 ? kGoesOn : 0)};
+    }
+    from = __shfl(at, G - 1, G);
   }
 }
 
@@ -372,10 +395,12 @@ gcn_status run_blocks(const AggParams& p, const BlockedPlan& b, const Piece* pie
   const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(most, (int64_t)p.n * panels / 32768));
   const dim3 grid((unsigned)(lr.groups + ceil_div(p.n, (int64_t)rounds * kWalkWaves)), (unsigned)panels);
   for (int32_t c = 0; c < b.nblock; ++c) {
-    if (c == b.nblock - 1)
-      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
+    if (b.nblock == 1)
+      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI, false>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, 1, rounds, lr);
+    else if (c == b.nblock - 1)
+      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI, true>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
     else
-      hipLaunchKernelGGL((k_agg_blocked<LANES, AGG_NONE>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
+      hipLaunchKernelGGL((k_agg_blocked<LANES, AGG_NONE, true>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
     GCN_TRY(check_launch("blocked aggregation"));
   }
   if (lr.groups > 0) {
@@ -489,8 +514,14 @@ gcn_status launch_agg_blocked(const AggParams& p, const BlockedPlan& b, const gc
   LongRows lr{};
   if (b.nblock > 1) {
     pieces = static_cast<Piece*>(ws);
-    hipLaunchKernelGGL(k_block_pieces, dim3((unsigned)ceil_div(p.n, 256)), dim3(256), 0, s, p.n, p.row_ptr, p.col, p.order,
-                       b.rows, b.nblock, pieces);
+    auto find = [&](auto lanes) {
+      constexpr int G = decltype(lanes)::value;
+      hipLaunchKernelGGL(k_block_pieces<G>, dim3((unsigned)ceil_div((int64_t)p.n * G, 256)), dim3(256), 0, s, p.n,
+                         p.row_ptr, p.col, p.order, b.rows, b.nblock, pieces);
+    };
+    if (b.nblock <= 4) find(std::integral_constant<int, 4>{});
+    else if (b.nblock <= 8) find(std::integral_constant<int, 8>{});
+    else find(std::integral_constant<int, 16>{});
     GCN_TRY(check_launch("row pieces"));
   } else if (has_split(split)) {
     lr.sp = *split;

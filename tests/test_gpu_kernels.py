@@ -1202,3 +1202,41 @@ def test_every_row_is_walked_once(G, orc, n):
     Z.fill_(float("nan"))
     G.aggregate_max_bwd(dg, dev(M), argd, Z)
     assert_mag_close(host(Z), orc.aggregate_max_backward(og, M, arg), orc.aggregate_max_backward(og, np.abs(M), arg), f"{n} rows, gradient")
+
+
+def test_blocked_sums_where_rows_miss_blocks(G, orc):
+    """Sums blocked by source rows on a graph whose rows have no entry in most blocks, in the first
+    one or in the last one (nodes joined to those around them; 100,000 rows, five blocks of 24,576
+    or nine of 12,288), with far pairs and a row of all kinds added: every epilogue and the loss."""
+    n, k = 100000, 250
+    i = np.arange(n, dtype=np.int32)
+    s = np.tile(i, k // 2)
+    d = np.concatenate([(i + j + 1) % n for j in range(k // 2)]).astype(np.int32)
+    rng = np.random.default_rng(2)
+    s = np.concatenate([s, np.full(3000, 60000, np.int32), rng.integers(0, n, 5000).astype(np.int32)])
+    d = np.concatenate([d, rng.permutation(n)[:3000].astype(np.int32), rng.integers(0, n, 5000).astype(np.int32)])
+    og, dg = orc.build_csr(n, s, d), G.build_csr(n, dev(s), dev(d))
+    assert og.nnz / n / 9 >= 24
+    rows = np.unique(np.concatenate([[0, 1, n - 1, 60000], rng.integers(0, n, 150), np.arange(24500, 24650, 3), s[-5000:-4900]]))
+    for w in (33, 128, 200):
+        M, b = rng.standard_normal((n, w)).astype(np.float32), rng.standard_normal(w).astype(np.float32)
+        mask = rng.standard_normal((n, w)).astype(np.float32)
+        ld = (w + 3) // 4 * 4
+        Md, Kd = pitched(M, ld), pitched(mask, ld)
+        for kind, agg in (("gcn", G.AGG_NORM), ("mean", G.AGG_MEAN), ("mean_t", G.AGG_MEAN_T)):
+            want, mag = orc.aggregate(og, M, b, rows=rows, want_mag=True, kind=kind)
+            for epi in (G.EPI_NONE, G.EPI_RELU, G.EPI_MASK):
+                Z = sentinel(np.zeros((n, w)), ld, 12345.0)
+                G.aggregate(dg, Md, Z, bias=dev(b), epi=epi, mask=Kd if epi == G.EPI_MASK else None, agg=agg)
+                full = want if epi == G.EPI_NONE else (np.maximum(want, 0) if epi == G.EPI_RELU else want * (mask[rows] > 0))
+                assert_mag_close(host(Z)[rows], full, mag, f"{kind} width {w} epi {epi}")
+                np.testing.assert_array_equal(padding_of(Z, ld), 12345.0)
+        y = rng.integers(0, w, n).astype(np.int32)
+        L = G.make_layer(w, w, ld, ld, G.ACT_SOFTMAX_CE, 1)
+        out, logits, loss = pitched(np.zeros((n, w)), ld), pitched(np.zeros((n, w)), ld), torch.zeros(1, device="cuda")
+        Mf = dev(np.zeros((n, ld), np.float32))
+        Mf[:, :w] = dev(M)
+        G.layer_fwd(dg, L, Mf[:, :w], None, dev(np.eye(w, dtype=np.float32)), dev(b), out, labels=dev(y), loss=loss, logits=logits)
+        want, mag = orc.aggregate(og, M, b, rows=rows, want_mag=True)
+        assert_mag_close(host(logits)[rows], want, mag, f"logits {w}")
+        assert_norm_close(host(out)[rows] * (n / rows.size), orc.softmax_ce(want, y[rows])[1], f"loss gradient {w}")
