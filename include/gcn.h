@@ -319,7 +319,7 @@ gcn_status gcn_epoch(gcn_model* m, const gcn_graph* g, const float* d_X, const g
  * d_M: n x w (pitch ldm).  d_bias: w or NULL.  epi: GCN_EPI_NONE, GCN_EPI_RELU
  * (max(Z, 0)) or GCN_EPI_MASK (Z * 1[mask > 0], d_mask n x w, pitch ldmask).
  * d_Z: n x w (pitch ldz); must not overlap d_M.  The workspace holds the chunk
- * sums of split hub rows (g->split.n_chunk x w floats, rounded up) or, on a dense
+ * sums of split hub rows (g->split.n_chunk x w floats, rounded up) and, on a dense
  * graph whose sums are blocked by source rows, the row pieces; with room for the
  * chunk sums alone the sums are not blocked (the same to rounding).
  */

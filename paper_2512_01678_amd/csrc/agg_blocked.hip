@@ -12,8 +12,8 @@
 // lines, so that no line is fetched for two panels.
 //
 // Long rows: a piece of more than kHub entries is cut over the four wavefronts of its
-// workgroup; rows beyond GCN_SPLIT_MIN with a split plan are summed chunk by chunk by
-// wavefronts that start ahead of the others in the same launch.  (On graphs of few rows the
+// workgroup; rows beyond GCN_SPLIT_MIN with a split plan (beyond that many per block where sums are
+// blocked) are summed chunk by chunk by wavefronts that start ahead of the others in the same launch.  (On graphs of few rows the
 // longest one bounds the call: 2,500 entries walked by one lane group took 110 us.)
 //
 // Dense graphs are blocked by source rows.  Gathered in row order, M is read from behind the L2
@@ -91,13 +91,18 @@ __device__ __forceinline__ void gather_eight(const char* Mc, uint32_t off, float
   gather_add<LANES, U, 4>(w, x, acc);
 }
 
-// Rows longer than GCN_SPLIT_MIN (one block only): `groups` workgroups ahead of the others sum
-// one chunk of such a row per wavefront into part (pitch pw); k_finish_long adds a row's chunks.
+// Rows of more than `over` entries: `groups` workgroups ahead of the others (in the first of several
+// launches) sum one chunk of such a row per wavefront into part (pitch pw); k_finish_long adds a
+// row's chunks.  over is GCN_SPLIT_MIN, or GCN_SPLIT_MIN per block: a chunk of such a row spans
+// about a block anyway, while its pieces, a workgroup each, would be the length of every launch
+// (200,000 rows of 128 and eight hubs of 190,000, width 64, 2,834 us in pieces, 855 so, 932
+// with lane groups).
 struct LongRows {
   gcn_split sp;
   float* part;
   int64_t pw;
   int32_t groups;
+  int64_t over;
 };
 
 // A row's partial sum, this lane's `left` columns of it: what lies beyond the width is the caller's.
@@ -183,16 +188,18 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
       const int64_t ch = lr.sp.order ? lr.sp.order[hi] : hi;
       const int32_t o = lr.sp.owner[ch], row = lr.sp.rows[o];
       h.beg = p.row_ptr[row] + (ch - lr.sp.first[o]) * (int64_t)GCN_SPLIT_CHUNK;
-      const int64_t left = p.row_ptr[row + 1] - h.beg;
-      h.len = (int)(left < GCN_SPLIT_CHUNK ? left : GCN_SPLIT_CHUNK);
-      h.row = (int)ch;
+      const int64_t end = p.row_ptr[row + 1], left = end - h.beg;
+      if (!BLOCKED || end - p.row_ptr[row] > lr.over) {
+        h.len = (int)(left < GCN_SPLIT_CHUNK ? left : GCN_SPLIT_CHUNK);
+        h.row = (int)ch;
+      }
     }
   } else if (L.lig < kWalkWaves * rounds && hi < p.n) {
     if (BLOCKED) {
       h = pieces[(int64_t)block * p.n + hi];
     } else {
       const int64_t beg = p.row_ptr[hi], end = p.row_ptr[hi + 1];
-      if (lr.groups == 0 || end - beg <= GCN_SPLIT_MIN) h = Piece{beg, (int32_t)(end - beg), (int32_t)hi};
+      if (lr.groups == 0 || end - beg <= lr.over) h = Piece{beg, (int32_t)(end - beg), (int32_t)hi};
     }
   }
   const Items items = make_items(h, rounds, wave, L.lig, !chunks);
@@ -312,12 +319,13 @@ __global__ void __launch_bounds__(kWalkThreads) k_finish_long(AggParams p, LongR
   L.c0 = ((int)blockIdx.y * LANES + L.lane) * 4;
   const int64_t o = ((int64_t)blockIdx.x * kWalkThreads + threadIdx.x) / LANES;
   if (o >= lr.sp.n_long) return;
+  const int64_t row = lr.sp.rows[o];
+  if (p.row_ptr[row + 1] - p.row_ptr[row] <= lr.over) return;  // summed piece by piece
   const bool cok = L.c0 < p.w;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   if (cok)
     for (int64_t ch = lr.sp.first[o]; ch < lr.sp.first[o + 1]; ++ch)
       Vec<4>::add(acc, *reinterpret_cast<const float4*>(lr.part + ch * lr.pw + L.c0));
-  const int64_t row = lr.sp.rows[o];
   if (EPI == AGG_SOFTMAX && gridDim.y > 1) {
     if (cok) store_sum(p.Z + row * p.ldz + L.c0, acc, p.w - L.c0);
   } else {
@@ -334,7 +342,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_finish_long(AggParams p, LongR
 template <int G>
 __global__ void __launch_bounds__(256) k_block_pieces(int32_t n, const int64_t* row_ptr, const int32_t* col,
                                                       const int32_t* order, int32_t rows, int32_t nblock,
-                                                      Piece* pieces) {
+                                                      int64_t over, Piece* pieces) {
   const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
   const int lane = threadIdx.x % G;
   if (i >= n) return;  // whole groups leave together
@@ -362,8 +370,9 @@ __global__ void __launch_bounds__(256) k_block_pieces(int32_t n, const int64_t* 
     int32_t start = __shfl_up(at, 1, G);
     if (lane == 0) start = from;
     if (b < nblock) {
-      const bool idle = at == start && b + 1 < nblock;  // no entry here: nothing to do before the end
-      pieces[(int64_t)b * n + i] = Piece{beg + start, at - start, idle ? -1 : row | (start > 0 ? kGoesOn : 0)};
+      // no entry here: nothing to do before the end; a long row: its chunks are summed elsewhere
+      const bool idle = (at == start && b + 1 < nblock) || len > over;
+      pieces[(int64_t)b * n + i] = Piece{beg + start, idle ? 0 : at - start, idle ? -1 : row | (start > 0 ? kGoesOn : 0)};
     }
     from = __shfl(at, G - 1, G);
   }
@@ -393,14 +402,16 @@ gcn_status run_blocks(const AggParams& p, const BlockedPlan& b, const Piece* pie
   // chip on small graphs and keep its end short (2 against 1 and 4: within 2 % on large ones)
   const int most = b.nblock > 1 || EPI == AGG_SOFTMAX ? kMaxRounds : 2;
   const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(most, (int64_t)p.n * panels / 32768));
-  const dim3 grid((unsigned)(lr.groups + ceil_div(p.n, (int64_t)rounds * kWalkWaves)), (unsigned)panels);
   for (int32_t c = 0; c < b.nblock; ++c) {
+    LongRows mine = lr;
+    if (c > 0) mine.groups = 0;
+    const dim3 grid((unsigned)(mine.groups + ceil_div(p.n, (int64_t)rounds * kWalkWaves)), (unsigned)panels);
     if (b.nblock == 1)
-      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI, false>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, 1, rounds, lr);
+      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI, false>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, 1, rounds, mine);
     else if (c == b.nblock - 1)
-      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI, true>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
+      hipLaunchKernelGGL((k_agg_blocked<LANES, EPI, true>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, mine);
     else
-      hipLaunchKernelGGL((k_agg_blocked<LANES, AGG_NONE, true>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, lr);
+      hipLaunchKernelGGL((k_agg_blocked<LANES, AGG_NONE, true>), grid, dim3(kWalkThreads), 0, s, p, pieces, c, b.nblock, rounds, mine);
     GCN_TRY(check_launch("blocked aggregation"));
   }
   if (lr.groups > 0) {
@@ -505,6 +516,7 @@ BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w
   return b;
 }
 
+// The row pieces of a blocked aggregation; the chunk sums of long rows come after them.
 size_t agg_blocked_workspace(const BlockedPlan& b, int64_t n) {
   return b.nblock > 1 ? sizeof(Piece) * (size_t)n * (size_t)b.nblock : 0;
 }
@@ -512,22 +524,25 @@ size_t agg_blocked_workspace(const BlockedPlan& b, int64_t n) {
 gcn_status launch_agg_blocked(const AggParams& p, const BlockedPlan& b, const gcn_split* split, void* ws, hipStream_t s) {
   Piece* pieces = nullptr;
   LongRows lr{};
+  lr.over = INT64_MAX;
+  if (has_split(split)) {
+    lr.sp = *split;
+    lr.part = reinterpret_cast<float*>(static_cast<char*>(ws) + agg_blocked_workspace(b, p.n));
+    lr.pw = round_up(p.w, 4);
+    lr.groups = (int32_t)ceil_div(split->n_chunk, kWalkWaves);
+    lr.over = (int64_t)GCN_SPLIT_MIN * b.nblock;
+  }
   if (b.nblock > 1) {
     pieces = static_cast<Piece*>(ws);
     auto find = [&](auto lanes) {
       constexpr int G = decltype(lanes)::value;
       hipLaunchKernelGGL(k_block_pieces<G>, dim3((unsigned)ceil_div((int64_t)p.n * G, 256)), dim3(256), 0, s, p.n,
-                         p.row_ptr, p.col, p.order, b.rows, b.nblock, pieces);
+                         p.row_ptr, p.col, p.order, b.rows, b.nblock, lr.over, pieces);
     };
     if (b.nblock <= 4) find(std::integral_constant<int, 4>{});
     else if (b.nblock <= 8) find(std::integral_constant<int, 8>{});
     else find(std::integral_constant<int, 16>{});
     GCN_TRY(check_launch("row pieces"));
-  } else if (has_split(split)) {
-    lr.sp = *split;
-    lr.part = static_cast<float*>(ws);
-    lr.pw = round_up(p.w, 4);
-    lr.groups = (int32_t)ceil_div(split->n_chunk, kWalkWaves);
   }
   switch (b.lanes) {
     case 4: return run_lanes<4>(p, b, pieces, lr, s);

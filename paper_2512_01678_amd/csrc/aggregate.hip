@@ -429,8 +429,8 @@ size_t aggregate_workspace(const gcn_split* split, int32_t w) {
 }
 
 size_t graph_aggregate_workspace(const gcn_graph* g, int32_t w, int64_t ldm, bool may_block) {
-  return std::max(aggregate_workspace(&g->split, w),
-                  agg_blocked_workspace(agg_blocked_plan(g->n, g->n, g->nnz, w, ldm, may_block), g->n));
+  return aggregate_workspace(&g->split, w) +
+         agg_blocked_workspace(agg_blocked_plan(g->n, g->n, g->nnz, w, ldm, may_block), g->n);
 }
 
 gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* split, void* ws,

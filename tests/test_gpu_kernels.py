@@ -1240,3 +1240,39 @@ def test_blocked_sums_where_rows_miss_blocks(G, orc):
         want, mag = orc.aggregate(og, M, b, rows=rows, want_mag=True)
         assert_mag_close(host(logits)[rows], want, mag, f"logits {w}")
         assert_norm_close(host(out)[rows] * (n / rows.size), orc.softmax_ce(want, y[rows])[1], f"loss gradient {w}")
+
+
+@pytest.mark.parametrize("w", [24, 41, 64, 100, 129, 256])
+def test_blocked_sums_with_hubs(G, orc, w):
+    """Rows so long that their chunks are summed apart from the blocks (beyond 4,096 entries per
+    block, two or three here: 20,000 always, 10,000 or 12,000 with two blocks), split rows that are
+    not (5,000, and a graph without a plan), each epilogue and the loss."""
+    n = 30000
+    rng = np.random.default_rng(w)
+    s, d = gs.chung_lu(n, 1100000, seed=3, dmax=3000.0)
+    for hub, ln in ((0, 20000), (7, 12000), (15001, 10000), (n - 1, 5000)):
+        s, d = np.concatenate([s, np.full(ln, hub, np.int32)]), np.concatenate([d, rng.permutation(n)[:ln].astype(np.int32)])
+    og = orc.build_csr(n, s, d)
+    rows = np.unique(np.concatenate([[0, 7, 15001, n - 1], rng.integers(0, n, 150)]))
+    M, b = rng.standard_normal((n, w)).astype(np.float32), rng.standard_normal(w).astype(np.float32)
+    mask, y = rng.standard_normal((n, w)).astype(np.float32), rng.integers(0, w, n).astype(np.int32)
+    ld = (w + 3) // 4 * 4
+    Mz = dev(np.zeros((n, ld), np.float32))
+    Mz[:, :w] = dev(M)
+    for split in (True, False):
+        dg = G.build_csr(n, dev(s), dev(d), split=split)
+        assert dg.n_long >= 4 or not split
+        for kind, agg in (("gcn", G.AGG_NORM), ("mean", G.AGG_MEAN)):
+            want, mag = orc.aggregate(og, M, b, rows=rows, want_mag=True, kind=kind)
+            for epi in (G.EPI_NONE, G.EPI_RELU, G.EPI_MASK):
+                Z = sentinel(np.full((n, w), np.nan), ld, 12345.0)
+                G.aggregate(dg, Mz[:, :w], Z, bias=dev(b), epi=epi, mask=pitched(mask, ld) if epi == G.EPI_MASK else None, agg=agg)
+                full = want if epi == G.EPI_NONE else (np.maximum(want, 0) if epi == G.EPI_RELU else want * (mask[rows] > 0))
+                assert_mag_close(host(Z)[rows], full, mag, f"{kind} width {w} epi {epi} split {split}")
+                assert np.isfinite(host(Z)).all()
+                np.testing.assert_array_equal(padding_of(Z, ld), 12345.0)
+            L = G.make_layer(w, w, ld, ld, G.ACT_SOFTMAX_CE, 1, agg=agg)
+            out, logits, loss = pitched(np.zeros((n, w)), ld), pitched(np.zeros((n, w)), ld), torch.zeros(1, device="cuda")
+            G.layer_fwd(dg, L, Mz[:, :w], None, dev(np.eye(w, dtype=np.float32)), dev(b), out, labels=dev(y), loss=loss, logits=logits)
+            assert_mag_close(host(logits)[rows], want, mag, f"logits {kind} {w} split {split}")
+            assert_norm_close(host(out)[rows] * (n / rows.size), orc.softmax_ce(want, y[rows])[1], f"loss gradient {kind} {w} split {split}")
