@@ -446,24 +446,36 @@ gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* piec
 }  // namespace
 
 // Panel and block of an aggregation of n rows with nnz entries from src_rows rows of M (pitch
-// ldm), w columns.  All lines measured with Chung-Lu graphs of 5,000 to 2,300,000 rows and 3 to
-// 490 entries per row; times in us, the lane groups of aggregate.hip first.
+// ldm), w columns.  All lines measured with Chung-Lu and uniform graphs of 2,000 to 2,300,000 rows
+// and 3 to 490 entries per row, and with matrices of uniform rows; times in us, the lane groups of
+// aggregate.hip first.
 //
 // Many rows of few entries leave most of a wavefront idle, and narrow ones gather little: they
-// stay with the lane groups, several rows to a wavefront (up to 16 columns 328,000 rows of 5 54
-// against 84, of 14 101 against 91; up to 32 columns 328,000 of 7 85 against 106, of 10 135
-// against 111; up to 64 columns of 3 68 against 98, of 5 125 against 104).  On fewer rows the
-// longest row decides, which a lane group walks by itself (20,000 of 65, width 7: 38 against 17).
+// stay with the lane groups, several rows to a wavefront.  Up to 8 columns, where those share long
+// rows, below 32 entries per row (8 columns, uniform and Chung-Lu, 100,000 rows of 6: 10 and 14
+// against 27 and 29; 200,000 of 24: 46 and 61 against 56 and 64; of 48: 88 and 128 against 85 and 92);
+// on up to 32,768 rows the longest one decides (20,000 of 6, width 4, Chung-Lu: 14 against 10).  Up
+// to 16 columns a group walks a long row by itself (100,000 rows of 3: 11 and 26 against 28 and 28;
+// of 6: 12 and 40 against 28 and 30; 400,000 of 12: 92 and 117 against 106 and 109); the rows of a
+// matrix are more alike than a graph's (100,000 of 12: 19 against 26; of 40: 46 against 32).  Up to
+// 32 columns 328,000 rows of 7: 85 against 106, of 10: 135 against 111; up to 64 columns of 3: 68
+// against 98, of 5: 125 against 104.  Rows of many 64-byte gathers from beyond the L2s gain from the
+// row order, which only the lane groups take (width 16, 150,000 rows of 400: 531 against 563; 284,480
+// of 306: 1,005 against 1,060; 400,000 of 200: 1,031 against 1,072, of 127: 686 against 680; 80,000
+// of 480: 297 against 302).  Built without an order they lose as much; the choice does not depend
+// on it, since results are the same with it and without.
 //
 // Panel: one slice per row where the row fits (4 lanes up to 16 columns, 8 up to 32, 16 up to 64,
 // 32 above); wider rows that start at line boundaries take 64-column panels of two lines
-// instead (width 256, 169,343 rows of 15: 306 against 335 with 32 lanes; RMAT 2^21 rows of 31
+// instead (width 256, 169,343 rows of 15: 306 against 340 with 32 lanes; RMAT 2^21 rows of 31
 // 7,170 against 7,718), since half of the panel fits the L2 twice, unless a row has too few
 // entries to pay for a second walk (1,000,000 rows of 3, width 128: 715; width 100 in one panel
-// 405; lane groups 476 and 461).  Where rows are not line-aligned a narrower panel would fetch
-// its edge lines twice (width 100, 2,449,029 rows: 8,790 in one panel, 12,900 in two).  32-column
-// panels pay where rows are gathered often and M is between the L2's size and a few times that
-// (100,000 rows of 64: 564 against 671; 50,000 of 32: 145 against 152; of 8: 106 against 63).
+// 405; lane groups 476 and 461).  (Where the gathers hit the L2, as with local ids, one panel would
+// be the better: 233,000 rows joined to the 16 around them, width 256, 312 against 214.)  Where rows
+// are not line-aligned a narrower panel would fetch its edge lines twice (width 100, 2,449,029 rows:
+// 8,790 in one panel, 12,900 in two).  32-column panels pay where rows are gathered often and M is
+// between the L2's size and a few times that (100,000 rows of 64: 564 against 671; 50,000 of 60,
+// width 128: 120 against 140; of 8: 106 against 63).
 //
 // Blocks: 6 MB panels of M (R1) where a row has 24 entries per block, else 12 MB ones (R2) where
 // it has 24 (100,000 rows of 128 entries, width 256: 957 with R1, 1,047 unblocked; 200,000 of
@@ -471,15 +483,21 @@ gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* piec
 // are twice the bytes and 12 suffice for R2 (200,000 of 128, width 100: 1,205 against 1,612).
 // Rows of one line (8 lanes) gain from larger blocks alone, and from 2^17 rows on (200,000 of
 // 128, width 24: 406 against 464; 100,000 of 128: 203 against 176).
-BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w, int64_t ldm, bool may_block) {
+BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w, int64_t ldm, RowKind kind,
+                             bool may_block) {
   BlockedPlan b{};
   if (w <= 0 || n <= 0 || nnz < 0 || src_rows <= 0 || 4 * src_rows * ldm > (int64_t)UINT32_MAX) return b;
   const double avg = (double)nnz / (double)n;
-  if (w <= 16 ? (n > 131072 && avg < 12) || (n > 400000 && avg < 16) : n > 65536 && (w <= 32 ? avg < 8 : w <= 64 && avg < 4))
+  const bool matrix = kind == ROWS_MATRIX;
+  if (w <= 8) {
+    if (n > 32768 && avg < 32) return b;
+  } else if (w <= 16) {
+    if ((n > 65536 && avg < 5) || (n > 131072 && avg < 12) || (n > 400000 && avg < 16)) return b;
+    if (matrix && n > 32768 && avg < 16) return b;
+    if (kind == ROWS_GRAPH && n > 131072 && avg >= 160) return b;
+  } else if (n > 65536 && (w <= 32 ? avg < 8 : w <= 64 && avg < 4)) {
     return b;
-  // many entries of 64-byte rows beyond the L2s: the lane groups with the row order (284,480 rows
-  // of 306, width 16, layer both ways 1,912 here, 2,048 with one row per wavefront)
-  if (may_block && w <= 16 && n > 262144 && avg >= 128) return b;
+  }
   if (w <= 16) {
     b.lanes = 4;
     b.nblock = 1;
@@ -509,7 +527,7 @@ BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w
   // two panels of rows that share lines, unblocked: the lane groups with the row order (layer both
   // ways, 717,618 rows of 176, width 152: 19,454 against 21,334; RMAT 2^19 rows of 33, width 246:
   // 5,328 against 5,661)
-  if (may_block && w > 128 && !lines && n > 400000) return BlockedPlan{};
+  if (kind == ROWS_GRAPH && w > 128 && !lines && n > 400000) return BlockedPlan{};
   // M in the L2 as it is (the weight of a sparse first layer): fewer passes over the entries
   if (w > 64 && n >= 32768 && 4 * src_rows * ldm <= (3 << 20)) b.lanes = 32;
   if (lines && w > 64 && avg >= 32 && src_rows >= 32768 && src_rows <= 400000) b.lanes = 8;

@@ -116,11 +116,13 @@ __device__ __forceinline__ First load_first(const AggParams& p, int64_t beg, int
 // sum_{e in [beg, end)} w_e M[col[e], c0 .. c0+VEC), every slice of the group holding the
 // total.  first: the group's first chunk of entries (load_first), already requested by
 // the caller.
-template <int LANES, int VEC>
+// UNR: loads kept in flight per lane.
+template <int LANES>
+constexpr int agg_unroll() { return LANES == 64 ? GCN_AGG_UNR : (LANES >= 4 ? 8 : 4); }
+template <int LANES, int VEC, int UNR = agg_unroll<LANES>()>
 __device__ __forceinline__ typename Vec<VEC>::T accumulate(const AggParams& p, int64_t beg, int64_t end,
                                                            const Lanes& L, int slots, bool cok, First first) {
   using V = Vec<VEC>;
-  constexpr int UNR = LANES == 64 ? GCN_AGG_UNR : (LANES >= 4 ? 8 : 4);
   typename V::T acc = V::zero();
   const float* Mc = p.M + L.c0;
   for (int64_t base = beg; base < end; base += L.gw) {

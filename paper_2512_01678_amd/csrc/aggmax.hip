@@ -458,7 +458,7 @@ static gcn_status launch_max(const MaxArgs& m, int64_t nnz, bool fwd, hipStream_
   // The panel of the linear aggregation (its own measurements); rows of dP and of the
   // maximisers are addressed by 32-bit offsets.
   if (vec4 && p.w > 16 && (fwd || 4 * p.src_rows * m.ldarg <= (int64_t)UINT32_MAX)) {
-    const BlockedPlan b = agg_blocked_plan(p.n, p.src_rows, nnz, p.w, p.ldm, false);
+    const BlockedPlan b = agg_blocked_plan(p.n, p.src_rows, nnz, p.w, p.ldm, ROWS_GRAPH_MAX, false);
     if (b.nblock > 0) {
       ProfScope prof(name, p.w, p.n, nnz, s);
       const int64_t panels = ceil_div(p.w, 4 * b.lanes);

@@ -35,45 +35,99 @@ namespace gcn {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kShareLanes = 2;  // rows of up to 8 columns: a group is a small part of a wavefront
 
 // Every row whose length is at most skip_over (all rows when there is no split plan).
 // One group per row; the hardware overlaps many resident wavefronts, which hides
 // the per-row chain of dependent loads better than prefetching across rows does.
 // Group g takes row p.order[g] when the graph carries a row order (long rows first:
 // they start early and the short rows fill the end of the launch), else row g.
+//
+// SHARE (narrow rows of 16-byte pieces): a row of more than share_over entries, which one group
+// would walk by itself while the others are long done, is summed by the whole workgroup, a quarter
+// per wavefront, after the workgroup's other rows; which rows those are depends on their lengths
+// alone.  (100,000 rows of 12, width 1, Chung-Lu 70 -> 21 us, uniform 10 -> 11.  At up to 16 columns
+// it would cost every other row a wavefront per SIMD: uniform 22 -> 25.)
 template <int LANES, int VEC, int EPI>
-__global__ void __launch_bounds__(kBlock) k_aggregate(AggParams p, int slots, int64_t skip_over) {
+__global__ void __launch_bounds__(kBlock) k_aggregate(AggParams p, int slots, int64_t skip_over, int64_t share_over) {
+  constexpr bool SHARE = VEC == 4 && LANES <= kShareLanes;
   const Lanes L = lanes_of<LANES, VEC>(slots);
   const bool cok = L.c0 < p.w;
-  const int64_t g = (int64_t)blockIdx.x * (kBlock / L.gw) + threadIdx.x / L.gw;
+  const int per = EPI == AGG_SOFTMAX ? slots : 1;  // consecutive rows of a group, in processing order
+  const int64_t row0 = ((int64_t)blockIdx.x * (kBlock / L.gw) + threadIdx.x / L.gw) * per;
+  // Rows to be shared, in any order: each one's sum is the same.
+  __shared__ int32_t s_rows[SHARE ? kBlock : 1], s_count;
+  if constexpr (SHARE) {
+    if (threadIdx.x == 0) s_count = 0;
+    __syncthreads();
+  }
+  auto share = [&](int64_t row) {
+    if (L.lig == 0) s_rows[atomicAdd(&s_count, 1)] = (int32_t)row;
+  };
   if constexpr (EPI == AGG_SOFTMAX) {
     // The loss epilogue (row maximum, exponentials, three slice reductions, the loss and
     // the gradient row) would cost every slice of a group the same instructions for one
     // row.  Instead a group sums `slots` consecutive rows one after the other, slice s
     // keeping row s's total, and then every slice finishes its own row.
-    const int64_t row0 = g * slots;
-    if (row0 >= p.n) return;  // whole groups leave together
-    typename Vec<VEC>::T mine = Vec<VEC>::zero();
-    bool own = false;
-    for (int r = 0; r < slots && row0 + r < p.n; ++r) {
-      const int64_t row = p.order ? p.order[row0 + r] : row0 + r;
-      const int64_t beg = p.row_ptr[row], end = p.row_ptr[row + 1];
-      if (end - beg > skip_over) continue;  // a long row: k_combine finishes it
-      const auto acc = accumulate<LANES, VEC>(p, beg, end, L, slots, cok, load_first<LANES>(p, beg, end, L));
-      if (L.slot == r) {
-        mine = acc;
-        own = true;
+    if (row0 < p.n) {  // whole groups
+      typename Vec<VEC>::T mine = Vec<VEC>::zero();
+      bool own = false;
+      for (int r = 0; r < slots && row0 + r < p.n; ++r) {
+        const int64_t row = p.order ? p.order[row0 + r] : row0 + r;
+        const int64_t beg = p.row_ptr[row], end = p.row_ptr[row + 1];
+        if (end - beg > skip_over) continue;  // a long row: k_combine finishes it
+        if (SHARE && end - beg > share_over) {
+          share(row);
+          continue;
+        }
+        const auto acc = accumulate<LANES, VEC>(p, beg, end, L, slots, cok, load_first<LANES>(p, beg, end, L));
+        if (L.slot == r) {
+          mine = acc;
+          own = true;
+        }
       }
+      const int64_t vr = row0 + L.slot;  // this slice's row, in processing order
+      finish_row<LANES, VEC, EPI, true>(p, p.order && vr < p.n ? p.order[vr] : vr, mine, L, cok, own);
     }
-    const int64_t vr = row0 + L.slot;  // this slice's row, in processing order
-    finish_row<LANES, VEC, EPI, true>(p, p.order && vr < p.n ? p.order[vr] : vr, mine, L, cok, own);
-  } else {
-    if (g >= p.n) return;  // whole groups leave together
-    const int64_t row = p.order ? p.order[g] : g;
+  } else if (row0 < p.n) {  // whole groups
+    const int64_t row = p.order ? p.order[row0] : row0;
     const int64_t beg = p.row_ptr[row], end = p.row_ptr[row + 1];
-    if (end - beg > skip_over) return;
-    const auto acc = accumulate<LANES, VEC>(p, beg, end, L, slots, cok, load_first<LANES>(p, beg, end, L));
-    finish_row<LANES, VEC, EPI>(p, row, acc, L, cok);
+    if (end - beg > skip_over) {
+      // a long row
+    } else if (SHARE && end - beg > share_over) {
+      share(row);
+    } else {
+      const auto acc = accumulate<LANES, VEC>(p, beg, end, L, slots, cok, load_first<LANES>(p, beg, end, L));
+      finish_row<LANES, VEC, EPI>(p, row, acc, L, cok);
+    }
+  }
+  if constexpr (SHARE) {
+    __syncthreads();
+    constexpr int kWaves = kBlock / 64;
+    __shared__ __attribute__((aligned(16))) float s_part[2][kWaves][VEC * LANES];
+    Lanes W = L;  // a whole wavefront's slices
+    W.gw = 64;
+    W.lig = threadIdx.x & 63;
+    W.slot = W.lig / LANES;
+    const int wave = threadIdx.x / 64;
+    int parity = 0;
+    for (int q = 0; q < s_count; ++q) {
+      const int64_t row = s_rows[q];
+      int64_t beg = p.row_ptr[row], end = p.row_ptr[row + 1];
+      const int64_t part = (end - beg + kWaves - 1) / kWaves;
+      beg += part * wave;
+      end = beg + part < end ? beg + part : end;
+      // half the loads in flight: more would cost the other rows a wavefront per SIMD
+      auto acc = accumulate<LANES, VEC, 4>(p, beg, end, W, 64 / LANES, cok, load_first<LANES>(p, beg, end, W));
+      float* const sp = s_part[parity][0] + VEC * L.lane;
+      parity ^= 1;
+      if (W.slot == 0) Vec<VEC>::store(sp + wave * VEC * LANES, acc);
+      __syncthreads();
+      if (wave != q % kWaves) continue;
+      acc = Vec<VEC>::zero();
+      for (int k = 0; k < kWaves; ++k) Vec<VEC>::add(acc, Vec<VEC>::load(sp + k * VEC * LANES));
+      finish_row<LANES, VEC, EPI>(p, row, acc, W, cok);
+    }
   }
 }
 
@@ -115,6 +169,7 @@ struct Launch {
   float* part;
   int64_t pw;
   int slots, chunk_slots;
+  int64_t share_over;
   hipStream_t s;
 };
 
@@ -128,7 +183,8 @@ gcn_status launch3(const Launch& a) {
     const int gw = LANES * a.slots;
     const int64_t groups = EPI == AGG_SOFTMAX ? ceil_div(p.n, a.slots) : p.n;  // rows per group
     dim3 grid((unsigned)ceil_div(groups, kBlock / gw), gy);
-    hipLaunchKernelGGL((k_aggregate<LANES, VEC, EPI>), grid, dim3(kBlock), 0, a.s, p, a.slots, skip);
+    hipLaunchKernelGGL((k_aggregate<LANES, VEC, EPI>), grid, dim3(kBlock), 0, a.s, p, a.slots, skip,
+                       a.share_over);
     GCN_TRY(check_launch("aggregate"));
   }
   if (!split) return GCN_OK;
@@ -430,7 +486,7 @@ size_t aggregate_workspace(const gcn_split* split, int32_t w) {
 
 size_t graph_aggregate_workspace(const gcn_graph* g, int32_t w, int64_t ldm, bool may_block) {
   return aggregate_workspace(&g->split, w) +
-         agg_blocked_workspace(agg_blocked_plan(g->n, g->n, g->nnz, w, ldm, may_block), g->n);
+         agg_blocked_workspace(agg_blocked_plan(g->n, g->n, g->nnz, w, ldm, ROWS_GRAPH, may_block), g->n);
 }
 
 gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* split, void* ws,
@@ -443,7 +499,7 @@ gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* sp
     // blocked sums rest in Z between the launches: not where the mask lies in it
     const bool mask_in_z = p.epi == AGG_MASK && p.mask < p.Z + (int64_t)p.n * p.ldz &&
                            p.Z < p.mask + (int64_t)p.n * p.ldmask;
-    const BlockedPlan b = agg_blocked_plan(p.n, p.src_rows, nnz, p.w, p.ldm, p.may_block && !mask_in_z);
+    const BlockedPlan b = agg_blocked_plan(p.n, p.src_rows, nnz, p.w, p.ldm, p.rows, p.may_block && !mask_in_z);
     if (b.nblock > 0 && (p.epi != AGG_SOFTMAX || p.w <= 256)) {
       if (!ws && (b.nblock > 1 || has_split(split)))
         return fail(GCN_E_INVALID, "aggregation: the workspace is missing");
@@ -477,7 +533,9 @@ gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* sp
   a.part = static_cast<float*>(ws);
   a.pw = round_up(p.w, 4);
   a.slots = pick_slots(lanes, nnz, p.n);
-  a.chunk_slots = std::min(64 / lanes, 16);
+  a.chunk_slots = 64 / lanes;
+  // six turns of a group's loads, and well above an average row
+  a.share_over = nnz >= 0 ? std::max<int64_t>(24 * a.slots, 4 * nnz / p.n) : INT64_MAX;
   a.s = s;
   ProfScope prof(name, p.w, p.n, nnz, s);
   return vec4 ? launch1<4>(a, lanes) : launch1<1>(a, lanes);

@@ -142,6 +142,7 @@ AggParams graph_agg(const gcn_graph* g, int32_t w, const float* M, int64_t ldm, 
   p.epi = AGG_NONE;
   p.order = g->order;
   p.src_rows = g->n;
+  p.rows = ROWS_GRAPH;
   p.may_block = may_block;
   return p;
 }

@@ -75,6 +75,10 @@ enum AggEpi { AGG_NONE = 0, AGG_RELU = 1, AGG_MASK = 2, AGG_SOFTMAX = 3 };
 //   AGG_W_COLMEAN  1 / deg[col[e]]        (transpose of the mean: (A + I) D^-1)
 enum AggWeight { AGG_W_VAL = 0, AGG_W_ONE = 1, AGG_W_ROWMEAN = 2, AGG_W_COLMEAN = 3 };
 
+// Rows of a matrix (X), of a graph (which may carry a row order), of a graph under the max walk
+// (which takes no order).
+enum RowKind { ROWS_MATRIX = 0, ROWS_GRAPH = 1, ROWS_GRAPH_MAX = 2 };
+
 struct AggParams {
   int32_t n;               // output rows
   const int64_t* row_ptr;  // n + 1
@@ -104,6 +108,7 @@ struct AggParams {
   // order in which the main kernel takes the rows (n entries), or NULL for 0 .. n-1
   const int32_t* order;
   int64_t src_rows;        // rows of M, or 0 (unknown)
+  RowKind rows;            // what the rows are
   bool may_block;          // ws has room for the blocked form (graph_aggregate_workspace)
 };
 // Words per row of a ReLU bitmask of width w.
@@ -114,7 +119,8 @@ struct BlockedPlan {
   int lanes;
   int32_t rows, nblock;
 };
-BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w, int64_t ldm, bool may_block);
+BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w, int64_t ldm, RowKind kind,
+                             bool may_block);
 size_t agg_blocked_workspace(const BlockedPlan& b, int64_t n);
 gcn_status launch_agg_blocked(const AggParams& p, const BlockedPlan& b, const gcn_split* split, void* ws, hipStream_t s);
 // Z over all rows; rows longer than GCN_SPLIT_MIN go through the split plan when one
