@@ -174,13 +174,13 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
   const char* Mc = reinterpret_cast<const char*>(p.M);
   const uint32_t lane_off = cok ? 4u * (uint32_t)L.c0 : 0u;  // lanes past the width re-read column 0 (not used)
   const uint32_t pitch = 4u * (uint32_t)p.ldm;
-  const bool last = block == nblock - 1;
+  const bool last = !BLOCKED || block == nblock - 1;
 
   // Lane 4 r + q holds the piece of round r, wavefront q: every wavefront knows all of them.
   const bool chunks = (int)blockIdx.x < lr.groups;
-  const int64_t ngroups = (int)gridDim.x - lr.groups;
-  const int64_t group = chunks ? (int64_t)blockIdx.x : walk_group((int)blockIdx.x - lr.groups, ngroups);
-  const int64_t hi = group * kWalkWaves + L.lig % kWalkWaves + (int64_t)(L.lig / kWalkWaves) * ngroups * kWalkWaves;
+  const uint32_t groups = gridDim.x - (uint32_t)lr.groups;
+  const uint32_t group = chunks ? blockIdx.x : walk_group(blockIdx.x - (uint32_t)lr.groups, groups);
+  const uint32_t hi = walk_row(group, groups, L.lig);
   Piece h{0, 0, -1};
   if (chunks) {
     rounds = 1;
@@ -194,7 +194,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_agg_blocked(AggParams p, const
         h.row = (int)ch;
       }
     }
-  } else if (L.lig < kWalkWaves * rounds && hi < p.n) {
+  } else if (L.lig < kWalkWaves * rounds && hi < (uint32_t)p.n) {
     if (BLOCKED) {
       h = pieces[(int64_t)block * p.n + hi];
     } else {

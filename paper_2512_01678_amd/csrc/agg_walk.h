@@ -50,10 +50,14 @@ __device__ __forceinline__ Lanes walk_lanes() {
 // workgroups take their places turned by a hash of which eight they are.  (2^20 rows of 31, RMAT
 // ids not permuted: width 40 2,494 -> 1,106 us, 256 6,294 -> 4,919, max aggregation of width 256
 // 14,431 -> 6,612, its gradient 27,894 -> 9,880; permuted ids the same.)
-__device__ __forceinline__ int64_t walk_group(int64_t b, int64_t groups) {
-  const int64_t eight = b >> 3;
+__device__ __forceinline__ uint32_t walk_group(uint32_t b, uint32_t groups) {
+  const uint32_t eight = b >> 3;
   if (8 * eight + 8 > groups) return b;
-  return (b & ~(int64_t)7) | ((b + (((uint32_t)eight * 0x9E3779B1u) >> 29)) & 7);
+  return (b & ~7u) | ((b + ((eight * 0x9E3779B1u) >> 29)) & 7u);
+}
+// The row of lane 4 r + q: round r, wavefront q of workgroup `group` of `groups`.
+__device__ __forceinline__ uint32_t walk_row(uint32_t group, uint32_t groups, int lig) {
+  return group * kWalkWaves + (uint32_t)lig % kWalkWaves + (uint32_t)lig / kWalkWaves * groups * kWalkWaves;
 }
 
 // What a wavefront does, item t in lane t: its own piece of a round, or its quarter of a shared

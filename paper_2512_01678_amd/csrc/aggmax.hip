@@ -199,10 +199,9 @@ __global__ void __launch_bounds__(kWalkThreads) k_walk_max(MaxArgs m, int32_t ro
   const char* Mc = reinterpret_cast<const char*>(p.M);
   const uint32_t lane_off = cok ? 4u * (uint32_t)L.c0 : 0u;
   const uint32_t pitch = 4u * (uint32_t)p.ldm;
-  const int64_t hi = walk_group(blockIdx.x, gridDim.x) * kWalkWaves + L.lig % kWalkWaves +
-                     (int64_t)(L.lig / kWalkWaves) * (int64_t)gridDim.x * kWalkWaves;
+  const uint32_t hi = walk_row(walk_group(blockIdx.x, gridDim.x), gridDim.x, L.lig);
   Piece h{0, 0, -1};
-  if (L.lig < kWalkWaves * rounds && hi < p.n)
+  if (L.lig < kWalkWaves * rounds && hi < (uint32_t)p.n)
     h = Piece{p.row_ptr[hi], (int32_t)(p.row_ptr[hi + 1] - p.row_ptr[hi]), (int32_t)hi};
   const Items items = make_items(h, rounds, wave, L.lig, true);
   Cursor<LANES> cursor;
@@ -328,10 +327,9 @@ __global__ void __launch_bounds__(kWalkThreads) k_walk_max_bwd(MaxArgs m, int32_
   const char* Ac = reinterpret_cast<const char*>(m.carg);
   const uint32_t lane_off = cok ? 4u * (uint32_t)L.c0 : 0u;
   const uint32_t dpitch = 4u * (uint32_t)p.ldm, apitch = 4u * (uint32_t)m.ldarg;
-  const int64_t hi = walk_group(blockIdx.x, gridDim.x) * kWalkWaves + L.lig % kWalkWaves +
-                     (int64_t)(L.lig / kWalkWaves) * (int64_t)gridDim.x * kWalkWaves;
+  const uint32_t hi = walk_row(walk_group(blockIdx.x, gridDim.x), gridDim.x, L.lig);
   Piece h{0, 0, -1};
-  if (L.lig < kWalkWaves * rounds && hi < p.n)
+  if (L.lig < kWalkWaves * rounds && hi < (uint32_t)p.n)
     h = Piece{p.row_ptr[hi], (int32_t)(p.row_ptr[hi + 1] - p.row_ptr[hi]), (int32_t)hi};
   const Items items = make_items(h, rounds, wave, L.lig, true);
   Cursor<LANES> cursor;
