@@ -454,7 +454,8 @@ gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* piec
 // stay with the lane groups, several rows to a wavefront.  Up to 8 columns, where those share long
 // rows, below 32 entries per row (8 columns, uniform and Chung-Lu, 100,000 rows of 6: 10 and 14
 // against 27 and 29; 200,000 of 24: 46 and 61 against 56 and 64; of 48: 88 and 128 against 85 and 92);
-// on up to 32,768 rows the longest one decides (20,000 of 6, width 4, Chung-Lu: 14 against 10).  Up
+// on up to 32,768 rows the longest one decides (20,000 of 6, width 4, Chung-Lu: 14 against 10); of a
+// matrix, whose M is in the L2, below 64 (1,048,576 of 41 from 4,096: 330 against 353).  Up
 // to 16 columns a group walks a long row by itself (100,000 rows of 3: 11 and 26 against 28 and 28;
 // of 6: 12 and 40 against 28 and 30; 400,000 of 12: 92 and 117 against 106 and 109); the rows of a
 // matrix are more alike than a graph's (100,000 of 12: 19 against 26; of 40: 46 against 32).  Up to
@@ -480,9 +481,14 @@ gcn_status run_lanes(const AggParams& p, const BlockedPlan& b, const Piece* piec
 // Blocks: 6 MB panels of M (R1) where a row has 24 entries per block, else 12 MB ones (R2) where
 // it has 24 (100,000 rows of 128 entries, width 256: 957 with R1, 1,047 unblocked; 200,000 of
 // 128: 2,429 with R2, 2,713 unblocked; of 64: 1,594 against 1,416).  With 32 lanes the entries
-// are twice the bytes and 12 suffice for R2 (200,000 of 128, width 100: 1,205 against 1,612).
-// Rows of one line (8 lanes) gain from larger blocks alone, and from 2^17 rows on (200,000 of
-// 128, width 24: 406 against 464; 100,000 of 128: 203 against 176).
+// are twice the bytes and from 131,072 rows on 12 suffice for R2 (200,000 of 128, width 100: 1,205
+// against 1,612; but 50,000 of 60: 222 against 161).  Each launch costs its start and its end, so few
+// entries in all don't pay: below 8 M with 16 lanes (Chung-Lu, width 64, 30,000 rows of 60: 81 against
+// 39; of 236: 112 against 117; 60,000 of 119: 163 against 163; 45,000 of 236: 149 against 215; uniform
+// 30,000 of 240: 117 against 132), below 3.5 M with 32 (width 100 and 200, Chung-Lu, 20,000 of 118: 106
+// against 82 and 173 against 186; of 235: 126 against 150 and 253 against 371; 45,000 of 60: 182 against
+// 143 and 303 against 300).  Rows of one line (8 lanes) gain from larger blocks alone, and from 2^17 rows
+// on (200,000 of 128, width 24: 406 against 464; 100,000 of 128: 203 against 176).
 BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w, int64_t ldm, RowKind kind,
                              bool may_block) {
   BlockedPlan b{};
@@ -490,7 +496,7 @@ BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w
   const double avg = (double)nnz / (double)n;
   const bool matrix = kind == ROWS_MATRIX;
   if (w <= 8) {
-    if (n > 32768 && avg < 32) return b;
+    if (n > 32768 && avg < (matrix ? 64 : 32)) return b;
   } else if (w <= 16) {
     if ((n > 65536 && avg < 5) || (n > 131072 && avg < 12) || (n > 400000 && avg < 16)) return b;
     if (matrix && n > 32768 && avg < 16) return b;
@@ -513,10 +519,9 @@ BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w
     int64_t rows = 0;
     if (b.lanes == 8) {
       if (src_rows >= (1 << 17) && entries(r1) >= 24) rows = r1;
-    } else if (entries(r1) >= 24) {
-      rows = r1;
-    } else if (entries(r2) >= (b.lanes == 32 ? 12 : 24)) {
-      rows = r2;
+    } else if (nnz >= (b.lanes == 16 ? 8000000 : 3500000)) {
+      if (entries(r1) >= 24) rows = r1;
+      else if (entries(r2) >= (b.lanes == 32 && src_rows >= 131072 ? 12 : 24)) rows = r2;
     }
     if (rows > 0 && src_rows > rows) {
       b.rows = (int32_t)rows;
@@ -524,12 +529,15 @@ BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w
       return b;
     }
   }
-  // two panels of rows that share lines, unblocked: the lane groups with the row order (layer both
-  // ways, 717,618 rows of 176, width 152: 19,454 against 21,334; RMAT 2^19 rows of 33, width 246:
-  // 5,328 against 5,661)
-  if (kind == ROWS_GRAPH && w > 128 && !lines && n > 400000) return BlockedPlan{};
-  // M in the L2 as it is (the weight of a sparse first layer): fewer passes over the entries
-  if (w > 64 && n >= 32768 && 4 * src_rows * ldm <= (3 << 20)) b.lanes = 32;
+  // Two panels of rows that share lines, unblocked: the lane groups with the row order (width 200,
+  // 169,343 rows of 15: 330 against 366; 400,000 of 200: 9,865 against 11,204; RMAT 2^19 rows of 33,
+  // width 246: 1,877 against 2,198; but 100,000 of 15, width 200: 204 against 203, 200,000 of 6: 212
+  // against 189).
+  if (kind == ROWS_GRAPH && w > 128 && !lines && (n > 400000 || (n > 131072 && avg >= 12))) return BlockedPlan{};
+  // M in the L2s as it is (the weight of a sparse first layer): fewer passes over the entries (1,048,576
+  // rows of 41 from 4,096, width 256: 1,891 against 2,241 in two panels, lane groups 2,065; 20,000 of 18
+  // from 1,433: 19 against 25 and 23)
+  if (w > 64 && n >= (matrix ? 8192 : 32768) && 4 * src_rows * ldm <= (matrix ? 8 << 20 : 3 << 20)) b.lanes = 32;
   if (lines && w > 64 && avg >= 32 && src_rows >= 32768 && src_rows <= 400000) b.lanes = 8;
   return b;
 }
