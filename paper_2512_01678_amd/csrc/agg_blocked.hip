@@ -495,6 +495,7 @@ BlockedPlan agg_blocked_plan(int64_t n, int64_t src_rows, int64_t nnz, int32_t w
   if (w <= 0 || n <= 0 || nnz < 0 || src_rows <= 0 || 4 * src_rows * ldm > (int64_t)UINT32_MAX) return b;
   const double avg = (double)nnz / (double)n;
   const bool matrix = kind == ROWS_MATRIX;
+  if (matrix && nnz > INT32_MAX) return b;  // a row may repeat columns and be longer than a piece counts
   if (w <= 8) {
     if (n > 32768 && avg < (matrix ? 64 : 32)) return b;
   } else if (w <= 16) {

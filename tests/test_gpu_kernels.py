@@ -1313,3 +1313,23 @@ def test_narrow_rows_by_groups_and_wavefronts(G, orc, n, e):
         want, mag = orc.aggregate(og, M, b, rows=rows, want_mag=True)
         assert_mag_close(host(logits)[rows], want, mag, f"logits {n} rows width {w}")
         assert_norm_close(host(out)[rows] * (n / rows.size), orc.softmax_ce(want, y[rows])[1], f"loss gradient {n} rows width {w}")
+
+
+def test_spmm_row_beyond_31_bits(G):
+    """gcn_spmm over a row of 2^31 + 9 entries (columns may repeat) among short ones."""
+    long_row, n = (1 << 31) + 9, 8
+    ln = torch.ones(n, dtype=torch.int64, device="cuda")
+    ln[3] = long_row
+    ptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    ptr[1:] = ln.cumsum(0)
+    note("a row of 2^31 + 9 entries")
+    nnz = int(ptr[-1])
+    idx, val = torch.zeros(nnz, dtype=torch.int32, device="cuda"), torch.ones(nnz, device="cuda")
+    val[-1] = 5.0
+    B = torch.tensor([[1.0, 2.0, 0.0, -1.0], [9.0, 9.0, 9.0, 9.0]], device="cuda")
+    out = torch.full((n, 4), float("nan"), device="cuda")
+    G.spmm(ptr, idx, val, B, out)
+    want = np.tile([1.0, 2.0, 0.0, -1.0], (n, 1))
+    want[3] *= long_row
+    want[n - 1] *= 5.0
+    np.testing.assert_allclose(host(out), want, rtol=1e-5)
