@@ -1333,3 +1333,24 @@ def test_spmm_row_beyond_31_bits(G):
     want[3] *= long_row
     want[n - 1] *= 5.0
     np.testing.assert_allclose(host(out), want, rtol=1e-5)
+
+
+@pytest.mark.parametrize("f,ld", [(1, 4), (5, 8), (32, 32), (33, 36), (61, 64), (64, 68), (65, 68), (127, 128), (128, 128)])
+def test_feature_views_narrow_rows(G, orc, f, ld):
+    """Rows of up to 128 columns, several to a wavefront: counts, bits and views byte for byte, few
+    rows and more than one turn of the grid, empty and full rows, NaN in the padding; dense rows of
+    the column view read four turns at a time (more than 64 nonzeros)."""
+    rng = np.random.default_rng(f)
+    for n, p in ((1, 1.0), (7, 0.5), (70001 if f > 8 else 600001, 0.03), (3000, 0.9)):
+        X = np.where(rng.random((n, f)) < p, rng.standard_normal((n, f)), 0.0).astype(np.float32)
+        X[n // 2] = np.inf
+        X[n - 1, f - 1] = -0.0
+        rnd = torch.zeros(n, dtype=torch.int64, device="cuda")
+        info, sx = G.feature_stats(pitched(X, ld), materialize=True, row_nnz=rnd)
+        nnz = int((X != 0).sum())
+        assert info["nnz"] == nnz
+        np.testing.assert_array_equal(host(rnd), (X != 0).sum(1))
+        for got, want in zip((sx.row_ptr, sx.col, sx.val), orc.dense_to_csr(X)):
+            np.testing.assert_array_equal(host(got)[:want.size], want)
+        for got, want in zip((sx.col_ptr, sx.row, sx.cval), orc.dense_to_csc(X)):
+            np.testing.assert_array_equal(host(got)[:want.size], want)
