@@ -430,7 +430,7 @@ constexpr int kLargeThreads = 512;
 __global__ void __launch_bounds__(kLargeThreads) k_sort_large(const int32_t* pcount, const int32_t* list, int32_t n,
                                                               int64_t* raw_off, const int32_t* cnt, const int32_t* raw,
                                                               int32_t* alt, int32_t* deg) {
-  constexpr int kWords = kWindow / 32, kPer = kWords / kLargeThreads;
+  constexpr int U = 16, kWords = kWindow / 32, kPer = kWords / kLargeThreads;
   __shared__ uint32_t bm[kWords];
   __shared__ int32_t wsum[kLargeThreads / 64];
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
@@ -444,9 +444,15 @@ __global__ void __launch_bounds__(kLargeThreads) k_sort_large(const int32_t* pco
     for (int64_t w0 = 0; w0 < n; w0 += kWindow) {
       for (int i = tid; i < kWords; i += kLargeThreads) bm[i] = 0;
       __syncthreads();
-      for (int32_t j = tid; j < len; j += kLargeThreads) {
-        const int64_t x = in[j] - w0;
-        if (x >= 0 && x < kWindow) atomicOr(&bm[x >> 5], 1u << (x & 31));
+      for (int64_t j = tid; j < len; j += U * kLargeThreads) {
+        int32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = j + u * kLargeThreads < len ? in[j + u * kLargeThreads] : -1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int64_t x = c[u] - w0;
+          if (c[u] >= 0 && x >= 0 && x < kWindow) atomicOr(&bm[x >> 5], 1u << (x & 31));
+        }
       }
       __syncthreads();
       // thread t reads words t * kPer ..; a scan over the workgroup gives its place
