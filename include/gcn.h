@@ -328,6 +328,14 @@ gcn_status gcn_aggregate(const gcn_graph* g, int32_t agg, int32_t w, const float
                          float* d_Z, int64_t ldz, void* d_ws, size_t* ws_bytes, hipStream_t stream);
 
 /*
+ * gcn_row_order_used -- 1 if gcn_aggregate over the graph at width w (16-byte aligned rows
+ * of M, pitch ldm) takes the rows in g->order when the graph carries one, so that its
+ * time depends on the order; 0 if it takes them as they come.  From the sizes alone
+ * (g->n, g->nnz): host only, no device memory is read.
+ */
+int32_t gcn_row_order_used(const gcn_graph* g, int32_t w, int64_t ldm);
+
+/*
  * gcn_aggregate_max -- max aggregation (GCN_AGG_MAX): P[u,c] = max over the row
  * of A + I of M[v,c] and arg[u,c] = the first v (lowest column) attaining it.
  * Asynchronous.  d_M: n x w (pitch ldm); d_P: n x w fp32 (pitch ldp); d_arg:

@@ -489,6 +489,23 @@ size_t graph_aggregate_workspace(const gcn_graph* g, int32_t w, int64_t ldm, boo
          agg_blocked_workspace(agg_blocked_plan(g->n, g->n, g->nnz, w, ldm, ROWS_GRAPH, may_block), g->n);
 }
 
+// The row order costs every row of a lane-group launch a scattered read of its offsets and a
+// scattered write of its output row; it pays where a row gathers enough bytes to hide that: taken
+// from 4 KB of gathered rows per average row on (measured on arxiv-like, 14.7 entries per row:
+// width 40 +18 % with the order, widths 128 and 256 -23 % and -10 %).
+static bool groups_take_order(int64_t n, int64_t nnz, int32_t w) {
+  return nnz < 0 || (double)nnz / (double)n * 4.0 * (double)w >= 4096.0;
+}
+
+bool row_order_used(const gcn_graph* g, int32_t w, int64_t ldm) {
+  if (g->n <= 0 || w <= 0) return false;
+  if (ldm % 4 == 0) {
+    const BlockedPlan b = agg_blocked_plan(g->n, g->n, g->nnz, w, ldm, ROWS_GRAPH, true);
+    if (b.nblock > 0) return b.nblock > 1;  // the walk takes rows as they come, the row pieces in order
+  }
+  return groups_take_order(g->n, g->nnz, w);
+}
+
 gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* split, void* ws,
                             hipStream_t s) {
   if (p.n == 0 || p.w == 0) return GCN_OK;
@@ -521,12 +538,8 @@ gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* sp
   if (p.epi == AGG_SOFTMAX && need > lanes)
     return fail(GCN_E_UNSUPPORTED, "softmax epilogue needs width <= 256 (vector) or 64 (scalar)");
   if (has_split(split) && !ws) return fail(GCN_E_INVALID, "aggregation of split rows needs a workspace");
-  // The row order costs every row a scattered read of its offsets and a scattered write of
-  // its output row; it pays where a row gathers enough bytes to hide that: taken from 4 KB
-  // of gathered rows per average row on (measured on arxiv-like, 14.7 entries per row:
-  // width 40 +18 % with the order, widths 128 and 256 -23 % and -10 %).
   AggParams q = p;
-  if (q.order && nnz >= 0 && (double)nnz / (double)p.n * 4.0 * (double)p.w < 4096.0) q.order = nullptr;
+  if (!groups_take_order(p.n, nnz, p.w)) q.order = nullptr;
   Launch a;
   a.p = &q;
   a.sp = split;

@@ -719,6 +719,10 @@ gcn_status gcn_aggregate(const gcn_graph* g, int32_t agg, int32_t w, const float
   return launch_aggregate(p, g->nnz, &g->split, d_ws, stream);
 }
 
+int32_t gcn_row_order_used(const gcn_graph* g, int32_t w, int64_t ldm) {
+  return g && ldm >= w && row_order_used(g, w, ldm) ? 1 : 0;
+}
+
 gcn_status gcn_aggregate_max(const gcn_graph* g, int32_t w, const float* d_M, int64_t ldm, float* d_P,
                              int64_t ldp, int32_t* d_arg, int64_t ldarg, void* d_ws, size_t* ws_bytes,
                              hipStream_t stream) {

@@ -131,6 +131,9 @@ size_t aggregate_workspace(const gcn_split* split, int32_t w);
 size_t graph_aggregate_workspace(const gcn_graph* g, int32_t w, int64_t ldm, bool may_block);
 gcn_status launch_aggregate(const AggParams& p, int64_t nnz, const gcn_split* split, void* ws,
                             hipStream_t s);
+// Whether a linear aggregation over the graph's rows (pitch ldm, 16-byte aligned) takes them in
+// the graph's row order.
+bool row_order_used(const gcn_graph* g, int32_t w, int64_t ldm);
 inline bool has_split(const gcn_split* sp) { return sp && sp->rows && sp->n_long > 0; }
 // Neighbour slices per row for slices of `lanes` lanes on a matrix with nnz entries over
 // `rows` rows (nnz < 0: unknown).

@@ -98,6 +98,7 @@ _SIG = {
                         P, C.POINTER(sz), P]),
     "gcn_aggregate": (i32, [C.POINTER(gcn_graph), i32, i32, P, i64, P, i32, P, i64, P, i64, P, C.POINTER(sz),
                             P]),
+    "gcn_row_order_used": (i32, [C.POINTER(gcn_graph), i32, i64]),
     "gcn_aggregate_max": (i32, [C.POINTER(gcn_graph), i32, P, i64, P, i64, P, i64, P, C.POINTER(sz), P]),
     "gcn_aggregate_max_bwd": (i32, [C.POINTER(gcn_graph), i32, P, i64, P, i64, P, i64, P, i64, P, C.POINTER(sz),
                                     P]),
@@ -236,10 +237,13 @@ def build_csr(n: int, src: torch.Tensor, dst: torch.Tensor, stream=None, split: 
 def tune_row_order(g: DeviceGraph, width: int, reps: int = 3) -> bool:
     """Keep the graph's row order (long rows first) only where it makes the aggregation of
     this width faster on this device: times gcn_aggregate both ways, twice each, and drops
-    the order when it does not win.  Every result is the same either way.  Returns whether
-    the order is kept."""
+    the order when it does not win.  An aggregation that takes rows as they come says
+    nothing about the order: it is then kept, untimed.  Every result is the same either way.
+    Returns whether the order is kept."""
     if g.order is None or g.n == 0:
         return False
+    if not _lib.gcn_row_order_used(C.byref(g.c), width, pitch(width)):
+        return True
     dev = g.row_ptr.device
     M = torch.zeros((g.n, pitch(width)), dtype=torch.float32, device=dev)[:, :width]
     Z = torch.empty_like(M)

@@ -85,6 +85,23 @@ def test_build_refuses_more_nodes_than_its_partition_tells_apart(G):
         assert "2^30" in L.gcn_last_error().decode()
 
 
+def test_row_order_used_by_sizes(G):
+    """Which aggregations take a graph's row order: blocked sums and lane groups over long rows do,
+    the row walk and lane groups over short rows don't."""
+    L = G.raw_lib()
+
+    def used(n, nnz, w):
+        g = G.gcn_graph(n, nnz, nnz, 1, 1, 1, 1, 1)
+        return L.gcn_row_order_used(C.byref(g), w, G.pitch(w))
+
+    assert used(232965, 114000000, 256) == 1   # blocked by source rows
+    assert used(2449029, 126000000, 256) == 0  # the walk
+    assert used(169343, 2500000, 40) == 0
+    assert used(169343, 2500000, 200) == 1     # lane groups, 11.8 KB per row
+    assert used(200000, 1200000, 8) == 0       # lane groups, 192 bytes per row
+    assert used(0, 0, 8) == 0 and L.gcn_row_order_used(None, 8, 8) == 0
+
+
 def test_host_validation_rejects_bad_calls(G):
     L = G.raw_lib()
     nb = G.sz(0)

@@ -1354,3 +1354,14 @@ def test_feature_views_narrow_rows(G, orc, f, ld):
             np.testing.assert_array_equal(host(got)[:want.size], want)
         for got, want in zip((sx.col_ptr, sx.row, sx.cval), orc.dense_to_csc(X)):
             np.testing.assert_array_equal(host(got)[:want.size], want)
+
+
+@pytest.mark.parametrize("w", [40, 128])
+def test_tune_row_order_keeps_what_it_cannot_time(G, w):
+    """An aggregation that takes the rows as they come cannot tell whether the order pays: the tuner
+    keeps it, every time."""
+    wl = gs.WORKLOADS["cora_like"]
+    s, d = gs.make_graph(wl)
+    for _ in range(20):
+        g = G.build_csr(wl.n, dev(s), dev(d))
+        assert G.tune_row_order(g, w) and g.order is not None and g.c.order == g.order.data_ptr()
