@@ -653,12 +653,9 @@ def test_tune_row_order(G, orc):
     np.testing.assert_array_equal(host(after), host(before))
 
 
-@pytest.mark.parametrize("fused", ["1", "0"])
 @pytest.mark.parametrize("fi,fo", [(128, 256), (48, 300)])
-def test_aggregate_first_layer_on_split_hubs(G, orc, hub_graph, fi, fo, fused, monkeypatch):
-    """Aggregate-then-transform layer, fused kernel and two-launch form: hub rows come from
-    the chunk kernels."""
-    monkeypatch.setenv("GCN_AF_FUSED", fused)
+def test_aggregate_first_layer_on_split_hubs(G, orc, hub_graph, fi, fo):
+    """Aggregate-then-transform layer: hub rows come from the chunk sums."""
     og, dg = hub_graph
     n = og.n
     rng = np.random.default_rng(fi)
@@ -1365,3 +1362,41 @@ def test_tune_row_order_keeps_what_it_cannot_time(G, w):
     for _ in range(20):
         g = G.build_csr(wl.n, dev(s), dev(d))
         assert G.tune_row_order(g, w) and g.order is not None and g.c.order == g.order.data_ptr()
+
+
+@pytest.mark.parametrize("n,e,widths", [(140000, 5900000, (17, 24, 32)), (140000, 1400000, (130, 200, 246)), (40000, 800000, (65, 96, 128, 256))])
+def test_plans_of_larger_graphs(G, orc, n, e, widths):
+    """The forms that only larger graphs take, checked on sampled rows: sums of rows of one line
+    blocked by source rows (from 131,072 rows on; every slice of a wavefront keeps a row of its own
+    for the loss), two panels of rows that share lines by lane groups in the row order, panels of 32
+    columns."""
+    s, d = gs.chung_lu(n, e, seed=9, dmax=6000.0)
+    og, dg = orc.build_csr(n, s, d), G.build_csr(n, dev(s), dev(d))
+    plain = G.build_csr(n, dev(s), dev(d), order=False)
+    avg = og.nnz / n
+    assert {17: avg >= 72, 130: 12 <= avg < 24, 65: avg >= 32}[widths[0]], avg
+    rng = np.random.default_rng(n + e)
+    rows = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 150), np.argsort(og.deg)[-20:], np.argsort(og.deg)[:20]]))
+    for w in widths:
+        ld = G.pitch(w)
+        M, b = rng.standard_normal((n, w)).astype(np.float32), rng.standard_normal(w).astype(np.float32)
+        mask, y = rng.standard_normal((n, w)).astype(np.float32), rng.integers(0, w, n).astype(np.int32)
+        Md, Kd = sentinel(M, ld, 7.0), pitched(mask, ld)
+        for kind, agg, epi in (("gcn", G.AGG_NORM, G.EPI_NONE), ("mean", G.AGG_MEAN, G.EPI_RELU), ("sum", G.AGG_SUM, G.EPI_MASK)):
+            outs = []
+            for g in (dg, plain):
+                Z = sentinel(np.full((n, w), np.nan), ld, 12345.0)
+                G.aggregate(g, Md, Z, bias=dev(b), epi=epi, mask=Kd if epi == G.EPI_MASK else None, agg=agg)
+                np.testing.assert_array_equal(padding_of(Z, ld), 12345.0)
+                outs.append(host(Z))
+            np.testing.assert_array_equal(*outs)
+            want, mag = orc.aggregate(og, M, b, rows=rows, want_mag=True, kind=kind)
+            want = want if epi == G.EPI_NONE else (np.maximum(want, 0) if epi == G.EPI_RELU else want * (mask[rows] > 0))
+            assert_mag_close(outs[0][rows], want, mag, f"{kind} {n} rows width {w} epi {epi}")
+        L = G.make_layer(w, w, ld, ld, G.ACT_SOFTMAX_CE, 1)
+        out, logits, loss = sentinel(np.zeros((n, w)), ld, 12345.0), sentinel(np.zeros((n, w)), ld, 12345.0), torch.zeros(1, device="cuda")
+        G.layer_fwd(dg, L, Md, None, dev(np.eye(w, dtype=np.float32)), dev(b), out, labels=dev(y), loss=loss, logits=logits)
+        want, mag = orc.aggregate(og, M, b, rows=rows, want_mag=True)
+        assert_mag_close(host(logits)[rows], want, mag, f"logits {n} rows width {w}")
+        assert_norm_close(host(out)[rows] * (n / rows.size), orc.softmax_ce(want, y[rows])[1], f"loss gradient {n} rows width {w}")
+        np.testing.assert_array_equal(padding_of(out, ld), 12345.0)

@@ -108,25 +108,23 @@ def test_layer_forward(G, orc, small, order, fi, fo, act):
 
 
 @pytest.mark.parametrize("fi,fo", [(128, 256), (100, 256), (41, 47), (64, 300)])
-def test_aggregate_first_fused_matches_two_launches(G, small, fi, fo, monkeypatch):
-    """The fused aggregate-then-transform kernel against the aggregation + GEMM pair:
-    the saved aggregate is bit-identical (same accumulation code), the output agrees
-    to fp32 rounding (same bf16x6 arithmetic, different grouping of k)."""
-    dg, n = small.dg, small.wl.n
+def test_aggregate_first_saved_and_output(G, orc, small, fi, fo):
+    """The aggregation and the product of an aggregate-first layer: the saved aggregate and the
+    output against the oracle, and the saved aggregate bit for bit that of gcn_aggregate."""
+    og, dg, n = small.og, small.dg, small.wl.n
     rng = np.random.default_rng(fi * fo)
     H = rng.standard_normal((n, fi)).astype(np.float32)
     W = (rng.standard_normal((fi, fo)) / np.sqrt(fi)).astype(np.float32)
     b = (rng.standard_normal(fo) * 0.1).astype(np.float32)
     L = G.make_layer(fi, fo, G.pitch(fi), G.pitch(fo), G.ACT_RELU, 0, G.AGGREGATE_FIRST)
-    res = {}
-    for mode in ("1", "0"):
-        monkeypatch.setenv("GCN_AF_FUSED", mode)
-        out, saved = G.padded(n, fo), G.padded(n, fi)
-        G.layer_fwd(dg, L, pad(G, H), None, dev(W), dev(b), out, saved=saved)
-        res[mode] = (host(out), host(saved))
-    np.testing.assert_array_equal(res["1"][1], res["0"][1])
-    scale = np.abs(res["0"][0]).max()
-    assert np.abs(res["1"][0] - res["0"][0]).max() <= 1e-5 * scale
+    out, saved, alone = G.padded(n, fo), G.padded(n, fi), G.padded(n, fi)
+    G.layer_fwd(dg, L, pad(G, H), None, dev(W), dev(b), out, saved=saved)
+    G.aggregate(dg, pad(G, H), alone)
+    np.testing.assert_array_equal(host(saved), host(alone))
+    P, pmag = orc.aggregate(og, H, want_mag=True)
+    assert_mag_close(host(saved), P, pmag, f"saved A_hat H {fi}")
+    Z, mag = orc.matmul(P, W) + b, orc.matmul(pmag, np.abs(W)) + np.abs(b)
+    assert_mag_close(host(out), np.maximum(Z, 0), mag, f"aggregate first {fi}->{fo}")
 
 
 @pytest.mark.parametrize("order", ["TF", "AF"])
@@ -515,6 +513,27 @@ def test_aggregator_layer_unit_parity(G, orc, small, agg, order):
         wmag = orc.matmul(Qm, np.abs(W).T) * (H > 0)
     assert_mag_close(host(db), Gr.astype(np.float64).sum(0), np.abs(Gr).astype(np.float64).sum(0), f"{agg} db")
     assert_mag_close(host(Gprev), want, wmag, f"{agg} {order} G_prev")
+
+
+@pytest.fixture(scope="module")
+def panels(G, orc):
+    wl = gs.Workload("panels", 40000, "chung_lu", 800000, (16, 128, 128), "normal", 1.0)
+    s, d = gs.chung_lu(wl.n, 800000, seed=11, dmax=5000.0)
+    p = Problem.__new__(Problem)
+    p.wl, p.og, p.dg = wl, orc.build_csr(wl.n, s, d), G.build_csr(wl.n, dev(s), dev(d))
+    p.X = np.random.default_rng(4).standard_normal((wl.n, 16)).astype(np.float32)
+    p.y = gs.labels(wl.n, 128)
+    p.Ws, p.bs = gs.make_weights(wl)
+    return p
+
+
+@pytest.mark.parametrize("aggs", [None, ("mean", "sum", "mean")])
+def test_epochs_narrow_panels(G, orc, panels, aggs):
+    """Line-aligned rows of 128 columns gathered in four panels of 32 (between 32,768 and 400,000 rows
+    of 32 entries and more): the ReLU bitmask, a word per panel, and the loss epilogue over sums of
+    several panels, in whole epochs."""
+    assert panels.og.nnz / panels.wl.n >= 32
+    run_epochs(G, orc, panels, 2, sparse=False, aggs=aggs)
 
 
 def test_epochs_forced_dense_on_sparse_features(G, orc, cora):
