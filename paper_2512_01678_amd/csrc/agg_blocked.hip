@@ -26,10 +26,12 @@
 // (with local ids a row's entries lie in one block or two: 232,965 rows joined to the 490 around
 // them, width 256, 6,452 -> 5,197 us).  Every sum has a fixed order: deterministic.
 //
-// Measured (us, before -> now, the same box): 232,965 rows of 484 entries, width 256 13,700 ->
-// 7,390, width 41 3,050 -> 1,930; 169,343 rows of 15, width 256 342 -> 306, 128 170 -> 157, 40
-// 106 -> 76; RMAT 2^21 rows of 31, width 128 4,000 -> 3,610; 2,449,029 rows of 51, width 256
-// 17,900 -> 17,600 (bound by the fabric); 100,000 rows of 32, width 128 272 -> 171.
+// Measured (us, lane groups -> now): 232,965 rows of 484 entries, width 256 13,700 -> 7,390, width
+// 41 3,050 -> 1,930; 169,343 rows of 15, width 256 335 -> 306, 128 169 -> 158, 64 108 -> 83; RMAT 2^21
+// rows of 31, width 128 4,000 -> 3,610; 2,449,029 rows of 51, width 256 17,900 -> 17,600 (bound by the
+// fabric); 100,000 rows of 32, width 128 272 -> 171.  Slower than the lane groups where ids are local,
+// whose gathers hit the L2 either way: 232,965 rows joined to the 490 around them, width 256 4,446 ->
+// 5,164, to the 16 around them 284 -> 314; 2,000,000 joined to 50 4,373 -> 4,842.
 #include "agg_walk.h"
 
 namespace gcn {
@@ -338,7 +340,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_finish_long(AggParams p, LongR
 // search, and the running maximum over the lanes makes the pieces make up the row whatever the
 // order of its columns; ascending ones (gcn_build_csr) make each block's gathers stay in it.
 // (Bound by the latency of the searches: one thread per row, block after block, took 202 us for
-// 232,965 rows and ten blocks, 70 now.)
+// 232,965 permuted rows of 490 and ten blocks, 134 now, 70 where ids are local.)
 template <int G>
 __global__ void __launch_bounds__(256) k_block_pieces(int32_t n, const int64_t* row_ptr, const int32_t* col,
                                                       const int32_t* order, int32_t rows, int32_t nblock,

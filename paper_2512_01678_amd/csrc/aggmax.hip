@@ -14,7 +14,9 @@
 // k_walk_max, k_walk_max_bwd); narrower and unaligned ones by lane groups, a long row by one of
 // them.  Both directions are bound as the linear aggregation is, by the gathers from behind the
 // L2; the gradient gathers two rows per entry (dP and the maximisers).  169,343 rows of 15, width
-// 128 (lane groups -> wavefronts): forward 274 -> 202 us, gradient 404 -> 346.
+// 128 (lane groups -> wavefronts): forward 274 -> 202 us, gradient 404 -> 346.  (With local ids, where
+// the gathers hit the L2, two panels cost more than one: 232,965 rows joined to the 16 around them,
+// width 256, forward 353 -> 475, gradient 411 -> 451.)
 #include "agg_walk.h"
 
 namespace gcn {

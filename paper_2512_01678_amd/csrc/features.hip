@@ -6,8 +6,9 @@
 // work (counts, offsets, index lists) plus bit-exact copies of the values, so
 // the results are identical to any other correct construction.
 //
-// X is read once to count (16-byte loads, a wavefront per row), leaving one bit per element in
-// the workspace when the views are wanted:
+// Every call reads X once to count (16-byte loads, a wavefront per row, or several narrow rows to
+// one), leaving one bit per element in the workspace when the views are wanted (a program that
+// counts first, to size the views, has X read by both calls):
 //  * DenseToCSR: a lane takes 32 columns' bits, a scan over the row's lanes gives its place, and
 //    only the nonzeros are read again; from one nonzero in 20 on, the row is read again whole
 //    and each nonzero placed by the popcount of the wavefront's ballot below its lane (columns

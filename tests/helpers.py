@@ -84,8 +84,8 @@ def adversarial_graphs():
 
 
 def note(msg):
-    """A progress line for long GPU tests: to stderr and appended to gpurun_out/test_progress.log
-    (a long test then shows activity while it runs)."""
+    """A progress line for long GPU tests: to stderr and appended to a progress file (a long test
+    then shows activity while it runs)."""
     import os
     import sys
     import time
