@@ -49,10 +49,11 @@ __device__ __forceinline__ Lanes walk_lanes() {
 // eighth group of four rows) one XCD would get most of the work.  So each eight consecutive
 // workgroups take their places turned by a hash of which eight they are.  (2^20 rows of 31, RMAT
 // ids not permuted: width 40 2,494 -> 1,106 us, 256 6,294 -> 4,919, max aggregation of width 256
-// 14,431 -> 6,612, its gradient 27,894 -> 9,880; permuted ids the same.)
+// 14,431 -> 6,612, its gradient 27,894 -> 9,880; 4,096 rows of 33, width 256 31 -> 23.  Permuted ids
+// lose up to 0.3 us a launch, which the smallest graphs would feel: 2,708 rows, an epoch of 65 us 0.9.)
 __device__ __forceinline__ uint32_t walk_group(uint32_t b, uint32_t groups) {
   const uint32_t eight = b >> 3;
-  if (8 * eight + 8 > groups) return b;
+  if (groups < 1024 || 8 * eight + 8 > groups) return b;
   return (b & ~7u) | ((b + ((eight * 0x9E3779B1u) >> 29)) & 7u);
 }
 // The row of lane 4 r + q: round r, wavefront q of workgroup `group` of `groups`.

@@ -1178,10 +1178,10 @@ def test_feature_views_with_the_counting_workspace(G, orc, csc):
             np.testing.assert_array_equal(host(sx.row)[:nnz], orc.dense_to_csc(X)[1])
 
 
-@pytest.mark.parametrize("n", [1, 2, 4, 5, 31, 32, 33, 64, 65, 96, 127, 129, 255, 257, 1000])
+@pytest.mark.parametrize("n", [1, 2, 5, 31, 33, 64, 257, 1000, 4093, 4096, 4101, 4124, 4129, 9001])
 def test_every_row_is_walked_once(G, orc, n):
-    """Workgroups of four rows take their places turned within each eight of them: every row comes
-    out, whatever is left over at the end of the eights."""
+    """Workgroups of four rows take their places turned within each eight of them, from 1,024 of them
+    on: every row comes out, whatever is left over at the end of the eights."""
     rng = np.random.default_rng(n)
     s, d = messy(rng, n, 5 * n)
     og, dg = orc.build_csr(n, s, d), G.build_csr(n, dev(s), dev(d))
